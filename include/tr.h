@@ -227,7 +227,9 @@ typedef struct {
   int32_t tile_w;            /* tile width in pixels: 4, 8, 16, 32 or 64; tiles hold 64
                                 pixels (default 64: one row segment per tile) */
   int32_t banks;             /* pixel banks (tiles in flight) per wave: 2 or 3 (queue depth) */
-  int32_t waves_per_cu;      /* persistent waves launched per compute unit, 1..32 */
+  int32_t waves_per_cu;      /* persistent waves launched per compute unit, 1..32; with
+                                the default here and in banks and stripe, and no stats
+                                buffer, one wave per tile or part of a tile instead */
   int32_t refill_below;      /* refill when fewer than this many lanes are busy, 1..64 */
   int32_t count_ops;         /* 1 = also fill the traversal counters of tr_frame.stats */
   int32_t accel;             /* 0 = walk the uniform grid; 1 = walk the scene's

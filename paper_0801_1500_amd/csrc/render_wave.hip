@@ -502,7 +502,27 @@ struct WaveArgs {
   uint64_t *stats;
   int32_t tile_w, refill_below;
   int32_t stripe_log2;  // tiles per stripe of the tile queue, log2
+  // launches of one workgroup per entry (BANKS = 1):
+  uint32_t whole;       // groups of 8 tiles that are entries as they are; the later tiles are split
+  int32_t part_log2;    // entries of a split tile, log2
 };
+
+// Entry of workgroup b in a launch of one workgroup per entry: 128 tile + (0
+// for a whole tile, part + 1 for one of 2^part_log2 equal parts of its
+// row-major pixels), or -1 past the launch's tiles.  Group j of 8 consecutive
+// tiles goes to the 8 XCDs, one tile each (workgroup b runs on XCD b mod 8),
+// rotated by a hash of j: without the rotation a frame of 8 k tiles a row
+// gives each XCD the same columns in every row, and the XCDs of the middle
+// columns finish last.
+__device__ __forceinline__ int64_t group_entry(const WaveArgs &A, uint32_t b) {
+  const uint32_t e = b / kQueueXcds;
+  const uint32_t split = e < A.whole ? 0u : e - A.whole;
+  const uint32_t j = e < A.whole ? e : A.whole + (split >> A.part_log2);
+  const uint32_t q = (b + ((j * 0x9E3779B1u) >> 29)) % kQueueXcds;
+  const int64_t tile = (int64_t)j * kQueueXcds + q;
+  const uint32_t part = e < A.whole ? 0u : (split & ((1u << A.part_log2) - 1u)) + 1u;
+  return tile < A.n_tiles ? (tile << 7) | part : -1;
+}
 
 __device__ __forceinline__ int32_t find_job(const TR_CONST JobDev *jobs, int32_t n, int64_t tile) {
   int32_t lo = 0, hi = n - 1;
@@ -514,12 +534,13 @@ __device__ __forceinline__ int32_t find_job(const TR_CONST JobDev *jobs, int32_t
   return lo;
 }
 
+// BANKS = 1: one workgroup per entry (group_entry), no tile queue.
 template <int BANKS, bool RESOLVE, bool COUNT, bool TRANS, bool TRI, bool BVH>
 // Occupancy targets: 5 waves per SIMD for the plain two-bank kernel (96
 // VGPRs); compositing adds LDS state that allows fewer waves anyway, and the
 // triangle test needs more registers than 96 without spilling; the BVH
 // walk's per-lane stacks (12 KB of LDS per wave) leave room for 2.
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? 2 : (TRANS ? 3 : (BANKS == 2 && !COUNT && !TRI ? 5 : 4))))) void k_render_wave(const WaveArgs A) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? 2 : (TRANS ? 3 : (BANKS <= 2 && !COUNT && !TRI ? 5 : 4))))) void k_render_wave(const WaveArgs A) {
   __shared__ Lds<BANKS, TRANS, BVH> L;
   constexpr int NS = BANKS * 64;
   constexpr int kMinIters = 2;
@@ -532,13 +553,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? 2 : (T
   int32_t q_head = 0, q_tail = 0, head_issued = 0;
   int32_t issue_bank = -1, issue_next = 0;
   uint32_t bank_busy = 0;
-  bool tiles_left = true;
+  constexpr bool SPLIT = BANKS == 1;
+  bool tiles_left = !SPLIT;
   int32_t xq = (int32_t)(blockIdx.x % kQueueXcds);  // tile queue drawn from: this XCD's first
   int32_t xq_left = kQueueXcds;                       // queues not yet found drained
-  int64_t held_tile = -1;
+  int64_t held_tile = -1;  // taken and not yet begun (SPLIT: a group_entry)
   int32_t held_job = 0, held_key = -1;
   int32_t cur_key = -1;   // scene loaded in this wave
   int32_t scene_job = 0;  // a job whose scene is the current one
+  if (SPLIT) {
+    held_tile = group_entry(A, blockIdx.x);
+    if (held_tile < 0) return;
+    held_job = scene_job = uni(find_job((const TR_CONST JobDev *)A.jobs, A.n_jobs, held_tile >> 7));
+  }
   int32_t idle_rounds = 0;
   bool stalled = false;  // left with work outstanding (reported in the stats)
 
@@ -874,6 +901,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? 2 : (T
           const uint32_t free_banks = ~bank_busy & ((1u << BANKS) - 1u);
           if (!free_banks) break;
           if (held_tile < 0) {
+            if (SPLIT) break;
             int64_t t = -1;
             while (tiles_left) {
               // the j-th tile of queue xq: tile j mod stripe of the queue's
@@ -897,7 +925,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? 2 : (T
             held_job = uni(find_job((const TR_CONST JobDev *)A.jobs, A.n_jobs, held_tile));
             held_key = uni(A.jobs[held_job].scene_key);
           }
-          if (held_key != cur_key) {
+          if (!SPLIT && held_key != cur_key) {
             if (bank_busy) break;  // drain this scene's banks before switching
             cur_key = held_key;
             scene_job = held_job;
@@ -905,11 +933,24 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? 2 : (T
           const TR_CONST JobDev *J = (const TR_CONST JobDev *)&A.jobs[held_job];
           const int32_t b = __ffs(free_banks) - 1;
           // tile index within its frame (< 2^31: the frame has < 2^31 pixels)
-          const uint32_t tl = (uint32_t)(held_tile - J->queue_begin + J->tile_begin);
+          const uint32_t tl =
+              (uint32_t)((SPLIT ? held_tile >> 7 : held_tile) - J->queue_begin + J->tile_begin);
           const uint32_t txs = (uint32_t)J->tiles_x;
           const int32_t ty = (int32_t)(tl / txs), tx = (int32_t)(tl - (uint32_t)ty * txs);
-          const int32_t x0 = tx * TW, y0 = ty * TH;
-          const int32_t vw = min(TW, J->W - x0), vh = min(TH, J->H - y0);
+          int32_t x0 = tx * TW, y0 = ty * TH, pw = TW, ph = TH;
+          if (SPLIT && (held_tile & 127)) {  // a part: 64 >> part_log2 pixels, row-major
+            const int32_t twl = __builtin_ctz((uint32_t)TW), pl = 6 - A.part_log2;
+            const int32_t q0 = ((int32_t)(held_tile & 127) - 1) << pl;
+            x0 += q0 & (TW - 1);
+            y0 += q0 >> twl;
+            pw = min(TW, 1 << pl);
+            ph = pl > twl ? 1 << (pl - twl) : 1;
+          }
+          const int32_t vw = min(pw, J->W - x0), vh = min(ph, J->H - y0);
+          if (SPLIT && (vw <= 0 || vh <= 0)) {  // a part beyond the frame's edge
+            held_tile = -1;
+            break;
+          }
           if (lane == 0) {
             BankInfo &B = L.bank[b];
             B.job = held_job;
@@ -1079,7 +1120,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? 2 : (T
       const uint32_t free_banks = ~bank_busy & ((1u << BANKS) - 1u);
       const bool can_refill =
           q_head != q_tail || (issue_bank >= 0 && issue_next < uni(L.bank[issue_bank].n)) ||
-          (free_banks && ((held_tile < 0 && tiles_left) || (held_tile >= 0 && (held_key == cur_key || !bank_busy))));
+          (free_banks && ((held_tile < 0 && tiles_left) || (held_tile >= 0 && (SPLIT || held_key == cur_key || !bank_busy))));
       const SceneHot H = load_hot(&A.jobs[uni(scene_job)]);
       // (>= 1, so the loop also ends when no lane works).  Lanes paused for
       // an FP64 re-solve wait for the loop's end: with a refill pending that
@@ -1519,6 +1560,9 @@ namespace trh {
 
 template <int BANKS, bool RES, bool CNT, bool TRANS, bool TRI, bool BVH = false>
 static hipError_t launch_t(const WaveLaunch &L, hipStream_t st) {
+  if constexpr (BANKS == 2 && !CNT) {
+    if (L.part_log2 >= 0) return launch_t<1, RES, CNT, TRANS, TRI, BVH>(L, st);
+  }
   WaveArgs a;
   a.jobs = L.jobs;
   a.n_jobs = L.n_jobs;
@@ -1528,6 +1572,8 @@ static hipError_t launch_t(const WaveLaunch &L, hipStream_t st) {
   a.tile_w = L.tile_w;
   a.refill_below = L.refill_below;
   a.stripe_log2 = __builtin_ctz((unsigned)L.stripe);
+  a.whole = L.whole;
+  a.part_log2 = L.part_log2;
   k_render_wave<BANKS, RES, CNT, TRANS, TRI, BVH><<<L.n_waves, 64, 0, st>>>(a);
   return hipGetLastError();
 }

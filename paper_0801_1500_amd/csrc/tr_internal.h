@@ -117,7 +117,11 @@ struct WaveLaunch {
   uint64_t *stats;           // device or null
   int32_t tile_w, banks, refill_below, count_ops;
   int32_t stripe;            // tiles per tile-queue stripe (a power of two)
-  int32_t n_waves;           // persistent waves launched
+  // One workgroup per entry (two banks asked for, no stats), or part_log2 = -1
+  // for persistent waves drawing from the tile queue:
+  uint32_t whole;            // groups of 8 tiles that are entries as they are
+  int32_t part_log2;         // entries of each later tile, log2
+  int32_t n_waves;           // waves launched
   int32_t resolve;
   int32_t trans;             // some job composites transparent layers
   int32_t tri;               // some job's scene has triangles
