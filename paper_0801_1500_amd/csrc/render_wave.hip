@@ -1525,13 +1525,20 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? 2 : (T
 
 __global__ void k_zero_u32(uint32_t *p) { *p = 0u; }
 
-// One job table entry written from a kernel argument (the caller's job needs
-// no host staging buffer): the wave copies its 4-byte words.
+// Job table entries written from a kernel argument (the caller's jobs need no
+// host staging buffer): one wave per job copies its 4-byte words.
 static_assert(sizeof(JobDev) % 4 == 0, "JobDev is copied as words");
-__global__ __launch_bounds__(64) void k_put_job(const JobDev J, JobDev *dst) {
-  const uint32_t *src = (const uint32_t *)&J;
-  uint32_t *d = (uint32_t *)dst;
-  for (uint32_t i = threadIdx.x; i < (uint32_t)(sizeof(JobDev) / 4); i += 64) d[i] = src[i];
+template <int N>
+struct JobArgs {
+  JobDev job[N];
+};
+static_assert(sizeof(JobArgs<trh::kPutJobs>) <= 4096, "kernel arguments are at most 4 KB");
+template <int N>
+__global__ __launch_bounds__(64) void k_put_jobs(const JobArgs<N> J, JobDev *dst) {
+  constexpr uint32_t words = (uint32_t)(sizeof(JobDev) / 4);
+  const uint32_t *src = (const uint32_t *)&J + blockIdx.x * words;
+  uint32_t *d = (uint32_t *)(dst + blockIdx.x);
+  for (uint32_t i = threadIdx.x; i < words; i += 64) d[i] = src[i];
 }
 
 __global__ void k_debug_philox(int64_t n, const uint32_t *ctr, const uint32_t *key, uint32_t *out) {
@@ -1613,8 +1620,20 @@ hipError_t launch_render_wave(const WaveLaunch &L, hipStream_t st) {
   return launch_b<2>(L, st);
 }
 
-hipError_t launch_put_job(const JobDev &J, JobDev *dst, hipStream_t st) {
-  k_put_job<<<1, 64, 0, st>>>(J, dst);
+template <int N>
+static void put_jobs(const JobDev *J, JobDev *dst, hipStream_t st) {
+  JobArgs<N> a;
+  for (int k = 0; k < N; ++k) a.job[k] = J[k];
+  k_put_jobs<N><<<N, 64, 0, st>>>(a, dst);
+}
+
+hipError_t launch_put_jobs(const JobDev *J, int32_t n, JobDev *dst, hipStream_t st) {
+  static_assert(kPutJobs == 3, "the launches below take 1 to 3 jobs");
+  for (; n > 0; n -= kPutJobs, J += kPutJobs, dst += kPutJobs) {
+    if (n >= 3) put_jobs<3>(J, dst, st);
+    else if (n == 2) put_jobs<2>(J, dst, st);
+    else put_jobs<1>(J, dst, st);
+  }
   return hipGetLastError();
 }
 

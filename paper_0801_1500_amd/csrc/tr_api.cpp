@@ -1014,15 +1014,16 @@ static tr_status make_job(const tr_scene *s, const tr_camera *c, const tr_params
 }
 
 // ------------------------------------------------------ launch resources
-// Per-stream ring of job tables: pinned staging + device table + tile
-// counter, each slot reusable once the launch that used it has completed.
+// Per-stream ring of job tables: device table, tile counter and, for tables of
+// more jobs than one launch writes from its arguments, pinned staging that is
+// reusable once the copy from it has run (the device parts are ordered by the
+// stream).
 struct LaunchSlot {
   JobDev *h_jobs = nullptr;
   JobDev *d_jobs = nullptr;
   uint32_t *d_counter = nullptr;  // tile queue counters + stall flag (kQueueWords)
-  int32_t cap = 0;
-  hipEvent_t done = nullptr;
-  bool used = false;
+  int32_t cap = 0, h_cap = 0;
+  hipEvent_t staged = nullptr;  // the last copy from h_jobs
 };
 struct StreamRing {
   LaunchSlot slot[4];
@@ -1050,20 +1051,29 @@ static tr_status acquire_slot(hipStream_t st, int32_t n, LaunchSlot **out) {
   StreamRing &ring = g_rings[{dev, st}];
   LaunchSlot &ls = ring.slot[ring.next];
   ring.next = (ring.next + 1) % 4;
-  if (ls.used) HIP_TRY(hipEventSynchronize(ls.done));
-  if (!ls.done) HIP_TRY(hipEventCreateWithFlags(&ls.done, hipEventDisableTiming));
   if (ls.cap < n) {
-    if (ls.h_jobs) (void)hipHostFree(ls.h_jobs);
-    if (ls.d_jobs) (void)hipFree(ls.d_jobs);
-    ls.h_jobs = nullptr;
+    if (ls.d_jobs) {  // launches enqueued on the stream may still read it
+      HIP_TRY(hipStreamSynchronize(st));
+      HIP_TRY(hipFree(ls.d_jobs));
+    }
     ls.d_jobs = nullptr;
-    int32_t cap = std::max(n, 8);
-    HIP_TRY(hipHostMalloc((void **)&ls.h_jobs, sizeof(JobDev) * cap, hipHostMallocDefault));
+    ls.cap = 0;
+    const int32_t cap = std::max(n, 8);
     HIP_TRY(hipMalloc((void **)&ls.d_jobs, sizeof(JobDev) * cap));
     ls.cap = cap;
   }
+  if (n > trh::kPutJobs) {
+    if (!ls.staged) HIP_TRY(hipEventCreateWithFlags(&ls.staged, hipEventDisableTiming));
+    HIP_TRY(hipEventSynchronize(ls.staged));  // (at once when never recorded)
+    if (ls.h_cap < n) {
+      if (ls.h_jobs) (void)hipHostFree(ls.h_jobs);
+      ls.h_jobs = nullptr;
+      ls.h_cap = 0;
+      HIP_TRY(hipHostMalloc((void **)&ls.h_jobs, sizeof(JobDev) * ls.cap, hipHostMallocDefault));
+      ls.h_cap = ls.cap;
+    }
+  }
   if (!ls.d_counter) HIP_TRY(hipMalloc((void **)&ls.d_counter, trd::kQueueWords * sizeof(uint32_t)));
-  ls.used = true;
   *out = &ls;
   return TR_OK;
 }
@@ -1285,13 +1295,17 @@ static tr_status launch_wave_jobs(std::vector<JobDev> &jobs, const tr_tune &t, u
   LaunchSlot *ls = nullptr;
   tr_status rc = acquire_slot(st, (int32_t)jobs.size(), &ls);
   if (rc != TR_OK) return rc;
-  std::memcpy(ls->h_jobs, jobs.data(), sizeof(JobDev) * jobs.size());
-  HIP_TRY(hipMemcpyAsync(ls->d_jobs, ls->h_jobs, sizeof(JobDev) * jobs.size(), hipMemcpyHostToDevice, st));
+  if (jobs.size() > (size_t)trh::kPutJobs) {
+    std::memcpy(ls->h_jobs, jobs.data(), sizeof(JobDev) * jobs.size());
+    HIP_TRY(hipMemcpyAsync(ls->d_jobs, ls->h_jobs, sizeof(JobDev) * jobs.size(), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipEventRecord(ls->staged, st));
+  } else {  // (a kernel of 2 us, where a copy is a staging buffer and an event besides)
+    HIP_TRY(trh::launch_put_jobs(jobs.data(), (int32_t)jobs.size(), ls->d_jobs, st));
+  }
   const trh::WaveLaunch L = wave_launch(jobs.data(), (int32_t)jobs.size(), total, t, stats,
                                         ls->d_jobs, ls->d_counter);
   if (L.part_log2 < 0) HIP_TRY(trh::launch_fill_u32(ls->d_counter, trd::kQueueWords, 0u, st));
   HIP_TRY(trh::launch_render_wave(L, st));
-  HIP_TRY(hipEventRecord(ls->done, st));
   return TR_OK;
 }
 
@@ -1493,7 +1507,7 @@ extern "C" tr_status tr_render_batch_noalloc(int32_t n, const tr_scene *const *s
   // write the table from kernel arguments, then render
   const trh::WaveLaunch L = wave_launch(jobs, nw, total, t, stats, S->jobs, S->counter);
   if (L.part_log2 < 0) HIP_TRY(trh::launch_fill_u32(S->counter, trd::kQueueWords, 0u, st));
-  for (int32_t k = 0; k < nw; ++k) HIP_TRY(trh::launch_put_job(jobs[k], &S->jobs[k], st));
+  HIP_TRY(trh::launch_put_jobs(jobs, nw, S->jobs, st));
   HIP_TRY(trh::launch_render_wave(L, st));
   return TR_OK;
 }

@@ -129,8 +129,10 @@ struct WaveLaunch {
 };
 hipError_t launch_render_wave(const WaveLaunch &L, hipStream_t st);
 hipError_t launch_zero_counter(uint32_t *p, hipStream_t st);
-// write one job table entry (device memory) from the host's job, by a kernel
-hipError_t launch_put_job(const trd::JobDev &J, trd::JobDev *dst, hipStream_t st);
+// write n job table entries (device memory) from the host's jobs, passed as
+// kernel arguments, kPutJobs a launch
+constexpr int kPutJobs = 3;
+hipError_t launch_put_jobs(const trd::JobDev *J, int32_t n, trd::JobDev *dst, hipStream_t st);
 
 // FP32 FMA rate (TFLOP/s) of non-packed v_fma_f32 over the whole device
 hipError_t measure_fma_rate(hipStream_t st, int32_t n_cus, double *tflops);
