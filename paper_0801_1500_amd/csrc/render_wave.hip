@@ -507,23 +507,6 @@ struct WaveArgs {
   int32_t part_log2;    // entries of a split tile, log2
 };
 
-// Entry of workgroup b in a launch of one workgroup per entry: 128 tile + (0
-// for a whole tile, part + 1 for one of 2^part_log2 equal parts of its
-// row-major pixels), or -1 past the launch's tiles.  Group j of 8 consecutive
-// tiles goes to the 8 XCDs, one tile each (workgroup b runs on XCD b mod 8),
-// rotated by a hash of j: without the rotation a frame of 8 k tiles a row
-// gives each XCD the same columns in every row, and the XCDs of the middle
-// columns finish last.
-__device__ __forceinline__ int64_t group_entry(const WaveArgs &A, uint32_t b) {
-  const uint32_t e = b / kQueueXcds;
-  const uint32_t split = e < A.whole ? 0u : e - A.whole;
-  const uint32_t j = e < A.whole ? e : A.whole + (split >> A.part_log2);
-  const uint32_t q = (b + ((j * 0x9E3779B1u) >> 29)) % kQueueXcds;
-  const int64_t tile = (int64_t)j * kQueueXcds + q;
-  const uint32_t part = e < A.whole ? 0u : (split & ((1u << A.part_log2) - 1u)) + 1u;
-  return tile < A.n_tiles ? (tile << 7) | part : -1;
-}
-
 __device__ __forceinline__ int32_t find_job(const TR_CONST JobDev *jobs, int32_t n, int64_t tile) {
   int32_t lo = 0, hi = n - 1;
   while (lo < hi) {
@@ -562,7 +545,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? 2 : (T
   int32_t cur_key = -1;   // scene loaded in this wave
   int32_t scene_job = 0;  // a job whose scene is the current one
   if (SPLIT) {
-    held_tile = group_entry(A, blockIdx.x);
+    held_tile = group_entry(blockIdx.x, A.whole, A.part_log2, A.n_tiles);
     if (held_tile < 0) return;
     held_job = scene_job = uni(find_job((const TR_CONST JobDev *)A.jobs, A.n_jobs, held_tile >> 7));
   }

@@ -1248,11 +1248,10 @@ static void set_entries(trh::WaveLaunch &L, int64_t total, const tr_tune &t) {
   if (t.banks != d.banks || t.waves_per_cu != d.waves_per_cu || t.stripe != d.stripe ||
       L.stats || total > ((int64_t)1 << 27))
     return;
-  const int64_t split = (int64_t)((L.n_jobs > 1 ? 20.0 : 60.0) * std::sqrt((double)total));
-  L.part_log2 = total <= 1024 ? 3 : 2;
-  if (total > 1024 && total > split) L.whole = (uint32_t)((total - split) / trd::kQueueXcds);
-  const int64_t groups = (total + trd::kQueueXcds - 1) / trd::kQueueXcds;
-  L.n_waves = (int32_t)((L.whole + ((groups - L.whole) << L.part_log2)) * trd::kQueueXcds);
+  const trh::Groups g = trh::split_groups(total, L.n_jobs);
+  L.whole = g.whole;
+  L.part_log2 = g.part_log2;
+  L.n_waves = (int32_t)g.workgroups;
 }
 
 // The launch of the wavefront kernel over n jobs (queue set) whose device

@@ -60,6 +60,24 @@ constexpr int kQueueXcds = 8;
 constexpr int kQueueStride = 32;  // words from one counter to the next
 constexpr int kQueueWords = (kQueueXcds + 1) * kQueueStride;
 
+// Entry of workgroup b in a launch of one workgroup per entry: 128 tile + (0
+// for a whole tile, part + 1 for one of 2^part_log2 equal parts of its
+// row-major pixels), or -1 past the launch's tiles.  Group j of 8 consecutive
+// tiles goes to the 8 XCDs, one tile each (workgroup b runs on XCD b mod 8),
+// rotated by a hash of j: without the rotation a frame of 8 k tiles a row
+// gives each XCD the same columns in every row, and the XCDs of the middle
+// columns finish last.
+__device__ __forceinline__ int64_t group_entry(uint32_t b, uint32_t whole, int32_t part_log2,
+                                               int64_t n_tiles) {
+  const uint32_t e = b / kQueueXcds;
+  const uint32_t split = e < whole ? 0u : e - whole;
+  const uint32_t j = e < whole ? e : whole + (split >> part_log2);
+  const uint32_t q = (b + ((j * 0x9E3779B1u) >> 29)) % kQueueXcds;
+  const int64_t tile = (int64_t)j * kQueueXcds + q;
+  const uint32_t part = e < whole ? 0u : (split & ((1u << part_log2) - 1u)) + 1u;
+  return tile < n_tiles ? (tile << 7) | part : -1;
+}
+
 // ----------------------------------------------------------------- scene
 struct SceneDev {
   int32_t n_s, n_c, n_t;  // ids: spheres, then cylinders, then triangles

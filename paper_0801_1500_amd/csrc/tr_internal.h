@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <string>
 
 #include "../../include/tr.h"
@@ -108,6 +109,24 @@ hipError_t launch_aa_mean(float *rgb, const float *planes, int32_t n_planes, int
 
 // ---- render launchers ----
 hipError_t launch_render_plain_f64(const trd::JobDev &job, uint64_t *stats, hipStream_t st);
+
+// Entries of a launch of one workgroup per entry over tiles of n_jobs frames
+// (trd::group_entry): the first 8 whole tiles as they are, each later one
+// in 2^part_log2 parts.
+struct Groups {
+  uint32_t whole;     // in groups of 8 tiles
+  int32_t part_log2;
+  int64_t workgroups;
+};
+inline Groups split_groups(int64_t tiles, int32_t n_jobs) {
+  const int64_t split = (int64_t)((n_jobs > 1 ? 20.0 : 60.0) * std::sqrt((double)tiles));
+  Groups g;
+  g.part_log2 = tiles <= 1024 ? 3 : 2;
+  g.whole = tiles > 1024 && tiles > split ? (uint32_t)((tiles - split) / trd::kQueueXcds) : 0u;
+  const int64_t groups = (tiles + trd::kQueueXcds - 1) / trd::kQueueXcds;
+  g.workgroups = (g.whole + ((groups - g.whole) << g.part_log2)) * trd::kQueueXcds;
+  return g;
+}
 
 struct WaveLaunch {
   const trd::JobDev *jobs;   // device array
