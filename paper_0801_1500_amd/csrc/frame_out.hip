@@ -13,6 +13,8 @@
 // Also here: the mean over an antialiased frame's sample planes, another
 // streaming pass (A * 4 bytes read and 4 written per value), and the
 // run-length Targa file of an 8-bit image (see k_tga_rows).
+#include <algorithm>
+
 #include "tr_internal.h"
 
 namespace {
@@ -72,23 +74,31 @@ __global__ __launch_bounds__(kThreads) void k_aa_mean(float *rgb, const float *p
 }
 
 // ---- Targa file, run-length true colour (the packet rule is written out
-// with the host-side declaration).  One wave per image row; each lane takes
-// kTgaPx adjacent pixels, so a step covers 64 * kTgaPx pixels and issues all
-// its byte loads at once.  A pixel's role follows from its neighbours alone:
-// it belongs to a run when it equals a neighbour; a segment (a maximal run
-// of one colour, or a maximal stretch of pixels in no run) starts where the
-// role changes or a run changes colour; packets are the 128-pixel pieces of
-// segments.  A pixel's segment starts at the last start at or before it: in
-// its own lane, else the last one of the lower lanes (a max scan), else the
-// segment still open from the previous step.  A run packet's 4 bytes belong
-// to its last pixel, a raw packet's header byte to its first, so a pixel's
-// byte position is the exclusive prefix sum of these sizes along the row.
-// Pass 1 sums each row, a scan turns the sums into row offsets, pass 2
-// recomputes the roles and writes.  The file is 18 header bytes, the rows,
-// 26 footer bytes.
+// with the host-side declaration).  One workgroup per image row; each thread
+// takes kTgaPx adjacent pixels.  A pixel's role follows from its neighbours
+// alone: it belongs to a run when it equals a neighbour; a segment (a maximal
+// run of one colour, or a maximal stretch of pixels in no run) starts where
+// the role changes or a run changes colour; packets are the 128-pixel pieces
+// of segments.  A pixel's segment starts at the last start at or before it: in
+// its own thread, else the last one of the lower threads (a max scan over the
+// workgroup), else the segment still open from the row's previous step.  A run
+// packet's 4 bytes belong to its last pixel, a raw packet's header byte to its
+// first, so a pixel's byte position is the exclusive prefix sum of these sizes
+// along the row.  Pass 1 sums each row, a scan turns the sums into row
+// offsets, pass 2 recomputes the roles and writes.  The file is 18 header
+// bytes, the rows, 26 footer bytes.
+//
+// Bound by HBM in principle (the image read twice, the file written once),
+// in fact by latency: one wave per row, 36 byte loads a lane and single-byte
+// stores took 55 and 73 us at 3860 x 4548.  The workgroup covers up to 8192
+// pixels at once, so a row is one step; a thread's pixels and their neighbours
+// are three loads of aligned words; their roles are bit masks, a dozen
+// operations for all eight (36 and 49 us with a compare and a select each);
+// and pass 2 puts the row's bytes together
+// in LDS and writes them out as words: 17 and 26 us.
 
 constexpr int kTgaHead = 18, kTgaFoot = 26;
-constexpr int kTgaPx = 8;  // pixels per lane per step
+constexpr int kTgaPx = 8;  // pixels per thread per step
 __constant__ char kTgaSig[18] = "TRUEVISION-XFILE.";  // footer signature (with its zero)
 
 __device__ __forceinline__ uint32_t px3(const uint8_t *row, int32_t x) {
@@ -96,110 +106,199 @@ __device__ __forceinline__ uint32_t px3(const uint8_t *row, int32_t x) {
   return (uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16);
 }
 
+typedef uint32_t vw4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t vw2 __attribute__((ext_vector_type(2), aligned(4)));
+
+// The 12 pixels from p (any alignment), R G B in the low bytes, from the ten
+// aligned words they lie in.
+__device__ __forceinline__ void load_px12(const uint8_t *p, uint32_t w[kTgaPx + 4]) {
+  const uint32_t sh = (uint32_t)((uintptr_t)p & 3u);
+  const uint32_t *a = (const uint32_t *)((uintptr_t)p & ~(uintptr_t)3);
+  const vw4 u0 = *(const vw4 *)a, u1 = *(const vw4 *)(a + 4);
+  const vw2 u2 = *(const vw2 *)(a + 8);
+  const uint32_t u[10] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w, u2.x, u2.y};
+  uint32_t v[9];
+#pragma unroll
+  for (int i = 0; i < 9; ++i) v[i] = __builtin_amdgcn_alignbyte(u[i + 1], u[i], sh);
+#pragma unroll
+  for (int k = 0; k < kTgaPx + 4; ++k) {
+    const int b = 3 * k, i = b >> 2, r = b & 3;
+    const uint32_t x = r < 2 ? v[i] >> (8 * r) : __builtin_amdgcn_alignbyte(v[i + 1], v[i], r);
+    w[k] = x & 0xFFFFFFu;
+  }
+}
+
+// Inclusive sum over the wave's lanes by DPP: shifts within each row of 16
+// lanes, then the sums of the rows before.
+__device__ __forceinline__ int32_t wave_sum_scan(int32_t x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1, 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2, 3
+  return x;
+}
+
 template <bool WRITE>
-__global__ __launch_bounds__(64) void k_tga_rows(const uint8_t *__restrict__ rgb, int32_t W,
-                                                 int64_t *__restrict__ row_bytes,
-                                                 const int64_t *__restrict__ row_off,
-                                                 uint8_t *__restrict__ out) {
+__global__ __launch_bounds__(1024) void k_tga_rows(const uint8_t *__restrict__ rgb, int32_t W,
+                                                   int32_t H, int64_t *__restrict__ row_bytes,
+                                                   const int64_t *__restrict__ row_off,
+                                                   const int64_t *__restrict__ total,
+                                                   uint8_t *__restrict__ out) {
+  extern __shared__ uint32_t stage32[];  // WRITE: the step's bytes, 4 a pixel at most, and 4 more
+  uint8_t *const stage = (uint8_t *)stage32;
+  __shared__ int32_t wave_start[16], wave_bytes[16];  // per wave: last segment start, bytes
   const int32_t y = blockIdx.x;
-  const int32_t lane = threadIdx.x;
+  const int32_t t = threadIdx.x, lane = t & 63, wv = t >> 6, n_wv = (int32_t)blockDim.x >> 6;
   const uint8_t *row = rgb + (int64_t)y * W * 3;
-  const int64_t base = WRITE ? row_off[y] : 0;
-  int64_t done = 0;      // bytes of the row before this step's pixels
+  const uint8_t *const img_end = rgb + (int64_t)H * W * 3;
+  if (WRITE && y == 0) {
+    // header (no image id or colour map, type 10, width, height, 24 bits, rows
+    // top first) and footer (no extension or developer area, the signature)
+    if (t < kTgaHead) {
+      uint8_t v = 0;
+      switch (t) {
+        case 2: v = 10; break;
+        case 12: v = (uint8_t)(W & 255); break;
+        case 13: v = (uint8_t)(W >> 8); break;
+        case 14: v = (uint8_t)(H & 255); break;
+        case 15: v = (uint8_t)(H >> 8); break;
+        case 16: v = 24; break;
+        case 17: v = 0x20; break;
+        default: break;
+      }
+      out[t] = v;
+    } else if (t < kTgaHead + kTgaFoot) {
+      const int32_t k = t - kTgaHead;  // footer byte
+      out[*total - kTgaFoot + k] = k < 8 ? (uint8_t)0 : (uint8_t)kTgaSig[k - 8];
+    }
+  }
+  int64_t done = WRITE ? row_off[y] : 0;  // WRITE: where the step's bytes go; else bytes so far
   int32_t open_seg = 0;  // first pixel of the segment still open at the step's start
-  for (int32_t x0 = 0; x0 < W; x0 += 64 * kTgaPx) {
-    const int32_t xb = x0 + kTgaPx * lane;  // this lane's first pixel
-    // the lane's pixels and two neighbours on each side
+  for (int32_t x0 = 0; x0 < W; x0 += (int32_t)blockDim.x * kTgaPx) {
+    const int32_t xb = x0 + kTgaPx * t;  // this thread's first pixel
+    // the thread's pixels and two neighbours on each side
+    // (bit k of the masks below: pixel xb - 2 + k)
     uint32_t w[kTgaPx + 4];
-    bool has[kTgaPx + 4];
+    const int32_t lo_k = max(0, 2 - xb), hi_k = min(kTgaPx + 4, W - xb + 2);
+    const uint32_t has = hi_k > lo_k ? ((1u << hi_k) - 1u) & ~((1u << lo_k) - 1u) : 0u;
+    const uint8_t *const p = row + 3 * (int64_t)(xb - 2);
+    const uintptr_t a = (uintptr_t)p & ~(uintptr_t)3;
+    if (a >= (uintptr_t)rgb && a + 40 <= (uintptr_t)img_end) {  // (within the image's bytes)
+      load_px12(p, w);
+    } else {
 #pragma unroll
-    for (int k = 0; k < kTgaPx + 4; ++k) {
-      const int32_t x = xb - 2 + k;
-      has[k] = x >= 0 && x < W;
-      w[k] = has[k] ? px3(row, x) : 0u;
+      for (int k = 0; k < kTgaPx + 4; ++k) w[k] = ((has >> k) & 1u) ? px3(row, xb - 2 + k) : 0u;
     }
-    bool run[kTgaPx], start[kTgaPx], end[kTgaPx];
-    int32_t last_start = -1;
+    uint32_t eq = 0;  // equal to the next pixel
 #pragma unroll
-    for (int j = 0; j < kTgaPx; ++j) {
-      const bool valid = has[j + 2];
-      const bool eq_l = valid && has[j + 1] && w[j + 2] == w[j + 1];
-      const bool eq_r = valid && has[j + 3] && w[j + 2] == w[j + 3];
-      run[j] = eq_l || eq_r;
-      const bool run_l = has[j + 1] && (eq_l || (has[j] && w[j + 1] == w[j]));  // pixel before
-      const bool run_r = has[j + 3] && (eq_r || (has[j + 4] && w[j + 3] == w[j + 4]));  // after
-      start[j] = valid && (!has[j + 1] || run[j] != run_l || (run[j] && !eq_l));
-      end[j] = valid && (!has[j + 3] || run[j] != run_r || (run_r && !eq_r));  // next one starts
-      if (start[j]) last_start = xb + j;
+    for (int k = 0; k < kTgaPx + 3; ++k) eq |= w[k] == w[k + 1] ? 1u << k : 0u;
+    eq &= has & (has >> 1);
+    constexpr uint32_t kMine = ((1u << kTgaPx) - 1u) << 2;
+    const uint32_t run = eq | (eq << 1);  // (of pixels 1 to 10)
+    // a segment starts at a row's first pixel, where the role changes, and in a
+    // run where the colour does; it ends where the next one starts
+    const uint32_t starts = has & (~(has << 1) | (run ^ (run << 1)) | (run & ~(eq << 1)));
+    const uint32_t ends = has & (~(has >> 1) | (starts >> 1));
+    const uint32_t mine = has & kMine;
+    const uint32_t my_starts = starts & kMine;
+    const int32_t last_start = my_starts ? xb - 2 + 31 - __builtin_clz(my_starts) : -1;
+    // last segment start of the threads below and of the wave
+    const uint64_t sm = __ballot(my_starts != 0);
+    const uint64_t lower = sm & ((1ull << lane) - 1ull);
+    const int32_t src = lower ? 63 - __builtin_clzll(lower) : 0;
+    int32_t below = __shfl(last_start, src);
+    if (!lower) below = -1;
+    const int32_t m = max(below, last_start);
+    if (lane == 63) wave_start[wv] = m;
+    __syncthreads();
+    int32_t step_last = -1;
+    for (int32_t k = 0; k < n_wv; ++k) {
+      const int32_t v = wave_start[k];
+      if (k < wv) below = max(below, v);
+      step_last = max(step_last, v);
     }
-    // last segment start of the lanes below (exclusive max scan) and of the wave
-    int32_t m = last_start;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int32_t v = __shfl_up(m, d);
-      if (lane >= d) m = max(m, v);
-    }
-    int32_t below = __shfl_up(m, 1);
-    if (lane == 0) below = -1;
-    const int32_t wave_last = __shfl(m, 63);
     const int32_t seg_before = below >= 0 ? below : open_seg;
-    int32_t kk[kTgaPx], bytes[kTgaPx];
-    int32_t seg_in = -1, lane_sum = 0;
-#pragma unroll
-    for (int j = 0; j < kTgaPx; ++j) {
-      if (start[j]) seg_in = xb + j;
-      const int32_t seg = seg_in >= 0 ? seg_in : seg_before;
-      kk[j] = (xb + j - seg) & 127;  // position in its packet
-      const bool first = kk[j] == 0, last = kk[j] == 127 || end[j];
-      bytes[j] = !has[j + 2] ? 0 : (run[j] ? (last ? 4 : 0) : (first ? 4 : 3));
-      lane_sum += bytes[j];
-    }
-    int32_t incl = lane_sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int32_t v = __shfl_up(incl, d);
-      if (lane >= d) incl += v;
+    // Packets: the open segment's may end and begin at one place here, 128
+    // pixels on (a segment that starts here has no second packet here).
+    const int32_t k_in = (xb - seg_before) & 127;  // position of the first pixel in its packet
+    const uint32_t open = my_starts ? (my_starts & -my_starts) - 1u : ~0u;  // before the first start
+    const int32_t cut = (128 - k_in) & 127;  // pixel (of mine) where a packet begins
+    const uint32_t cut_bit = cut < kTgaPx ? (4u << cut) & open : 0u;
+    const uint32_t cut_end = k_in + kTgaPx > 127 ? (4u << (127 - k_in)) & open : 0u;
+    const uint32_t firsts = (starts | cut_bit) & mine, lasts = (ends | cut_end) & mine;
+    const uint32_t raw = mine & ~run;
+    const int32_t sum = 3 * __popc(raw) + __popc(raw & firsts) + 4 * __popc(mine & run & lasts);
+    const int32_t incl = wave_sum_scan(sum);
+    if (lane == 63) wave_bytes[wv] = incl;
+    __syncthreads();
+    int32_t before = 0, step_bytes = 0;
+    for (int32_t k = 0; k < n_wv; ++k) {
+      const int32_t v = wave_bytes[k];
+      if (k < wv) before += v;
+      step_bytes += v;
     }
     if (WRITE) {
-      int64_t pos = base + done + (incl - lane_sum);
+      // byte `at` of the step is stage[off + at]: words of the stage and of the
+      // file then have the same alignment
+      const int32_t off = (int32_t)((uintptr_t)(out + done) & 3u);
+      int32_t at = before + incl - sum, kk = k_in - 1;
 #pragma unroll
       for (int j = 0; j < kTgaPx; ++j) {
-        if (has[j + 2]) {
-          const uint32_t p0 = w[j + 2];
-          const uint8_t r = (uint8_t)(p0 & 255u), g = (uint8_t)((p0 >> 8) & 255u),
-                        b = (uint8_t)(p0 >> 16);
-          const bool first = kk[j] == 0, last = kk[j] == 127 || end[j];
-          if (run[j]) {
-            if (last) {
-              out[pos] = (uint8_t)(0x80 | kk[j]);
-              out[pos + 1] = b;
-              out[pos + 2] = g;
-              out[pos + 3] = r;
-            }
-          } else {
-            const int64_t q = pos + (first ? 1 : 0);
-            out[q] = b;
-            out[q + 1] = g;
-            out[q + 2] = r;
-            // the header sits before the packet's first pixel: 1 + 3 kk bytes back
-            if (last) out[first ? pos : pos - 1 - 3 * (int64_t)kk[j]] = (uint8_t)kk[j];
+        const uint32_t bit = 4u << j;
+        kk = (firsts & bit) ? 0 : kk + 1;  // position in its packet
+        const uint32_t p0 = w[j + 2];
+        const uint8_t r = (uint8_t)(p0 & 255u), g = (uint8_t)((p0 >> 8) & 255u), b = (uint8_t)(p0 >> 16);
+        if (raw & bit) {
+          uint8_t *const q = stage + off + at + ((firsts & bit) ? 1 : 0);
+          q[0] = b;
+          q[1] = g;
+          q[2] = r;
+          // the header sits before the packet's first pixel: 1 + 3 kk bytes
+          // back, in the file already when that was in the previous step
+          // (whose stores the barriers since have completed)
+          if (lasts & bit) {
+            const int32_t ha = (firsts & bit) ? at : at - 1 - 3 * kk;
+            if (ha >= 0) stage[off + ha] = (uint8_t)kk;
+            else out[done + ha] = (uint8_t)kk;
           }
+          at += (firsts & bit) ? 4 : 3;
+        } else if (mine & lasts & bit) {
+          uint8_t *const q = stage + off + at;
+          q[0] = (uint8_t)(0x80 | kk);
+          q[1] = b;
+          q[2] = g;
+          q[3] = r;
+          at += 4;
         }
-        pos += bytes[j];
+      }
+      __syncthreads();
+      // whole words of the file, then the bytes before and after them
+      uint8_t *const base = out + done - off;  // (word-aligned)
+      const int32_t lo = off ? 1 : 0, hi = (off + step_bytes) >> 2;
+      for (int32_t i = lo + t; i < hi; i += (int32_t)blockDim.x) ((uint32_t *)base)[i] = stage32[i];
+      if (hi < lo) {  // all within one word
+        if (t >= off && t < off + step_bytes) base[t] = stage[t];
+      } else {
+        if (t >= off && t < 4 * lo) base[t] = stage[t];
+        if (t < 4 && 4 * hi + t < off + step_bytes) base[4 * hi + t] = stage[4 * hi + t];
       }
     }
-    done += __shfl(incl, 63);
-    if (wave_last >= 0) open_seg = wave_last;
+    done += step_bytes;
+    if (step_last >= 0) open_seg = step_last;
+    __syncthreads();  // (the shared arrays are free for the next step)
   }
-  if (!WRITE && lane == 0) row_bytes[y] = done;
+  if (!WRITE && t == 0) row_bytes[y] = done;
 }
 
 // Row offsets (exclusive sum of row sizes, after the header) and the file
-// size, in one workgroup: each thread sums a contiguous block of rows, the
+// size (also to pinned host memory), in one workgroup: each thread sums a contiguous block of rows, the
 // block sums are scanned in LDS, then each thread writes its rows' offsets.
 __global__ __launch_bounds__(1024) void k_tga_offsets(const int64_t *__restrict__ row_bytes,
                                                       int32_t H, int64_t *__restrict__ row_off,
-                                                      int64_t *__restrict__ total) {
+                                                      int64_t *__restrict__ total,
+                                                      int64_t *__restrict__ h_total) {
   __shared__ int64_t part[1024];
   const int32_t t = threadIdx.x;
   const int32_t per = (H + 1023) / 1024;
@@ -219,32 +318,7 @@ __global__ __launch_bounds__(1024) void k_tga_offsets(const int64_t *__restrict_
     row_off[i] = at;
     at += row_bytes[i];
   }
-  if (t == 1023) *total = kTgaHead + part[1023] + kTgaFoot;
-}
-
-// Header (no image id or colour map, type 10, width, height, 24 bits, rows
-// top first) and footer (no extension or developer area, the signature).
-__global__ __launch_bounds__(64) void k_tga_frame(int32_t W, int32_t H,
-                                                  const int64_t *__restrict__ total,
-                                                  uint8_t *__restrict__ out) {
-  const int32_t t = threadIdx.x;
-  if (t < kTgaHead) {
-    uint8_t v = 0;
-    switch (t) {
-      case 2: v = 10; break;
-      case 12: v = (uint8_t)(W & 255); break;
-      case 13: v = (uint8_t)(W >> 8); break;
-      case 14: v = (uint8_t)(H & 255); break;
-      case 15: v = (uint8_t)(H >> 8); break;
-      case 16: v = 24; break;
-      case 17: v = 0x20; break;
-      default: break;
-    }
-    out[t] = v;
-  } else if (t < kTgaHead + kTgaFoot) {
-    const int32_t k = t - kTgaHead;  // footer byte
-    out[*total - kTgaFoot + k] = k < 8 ? (uint8_t)0 : (uint8_t)kTgaSig[k - 8];
-  }
+  if (t == 1023) *total = *h_total = kTgaHead + part[1023] + kTgaFoot;
 }
 
 }  // namespace
@@ -286,17 +360,23 @@ hipError_t launch_quantize_rgb8(const float *in, int64_t n, uint8_t *out, hipStr
 
 namespace trh {
 
+// Threads per row: enough for the row in one step, in whole waves.
+static unsigned tga_threads(int32_t W) {
+  const int n = (W + kTgaPx - 1) / kTgaPx;
+  return (unsigned)std::min(1024, (n + 63) / 64 * 64);
+}
+
 hipError_t launch_tga_sizes(const uint8_t *rgb, int32_t W, int32_t H, int64_t *row_bytes,
-                            int64_t *row_off, int64_t *total, hipStream_t st) {
-  k_tga_rows<false><<<(unsigned)H, 64, 0, st>>>(rgb, W, row_bytes, nullptr, nullptr);
-  k_tga_offsets<<<1, 1024, 0, st>>>(row_bytes, H, row_off, total);
+                            int64_t *row_off, int64_t *total, int64_t *h_total, hipStream_t st) {
+  k_tga_rows<false><<<(unsigned)H, tga_threads(W), 0, st>>>(rgb, W, H, row_bytes, nullptr, nullptr, nullptr);
+  k_tga_offsets<<<1, 1024, 0, st>>>(row_bytes, H, row_off, total, h_total);
   return hipGetLastError();
 }
 
 hipError_t launch_tga_write(const uint8_t *rgb, int32_t W, int32_t H, const int64_t *row_off,
                             const int64_t *total, uint8_t *out, hipStream_t st) {
-  k_tga_rows<true><<<(unsigned)H, 64, 0, st>>>(rgb, W, nullptr, row_off, out);
-  k_tga_frame<<<1, 64, 0, st>>>(W, H, total, out);
+  const unsigned n = tga_threads(W);
+  k_tga_rows<true><<<(unsigned)H, n, n * kTgaPx * 4 + 8, st>>>(rgb, W, H, nullptr, row_off, total, out);
   return hipGetLastError();
 }
 

@@ -1577,8 +1577,7 @@ extern "C" tr_status tr_frame_encode_tga(const uint8_t *rgb8, int32_t width, int
   }
   if (!w.h_total) HIP_TRY(hipHostMalloc((void **)&w.h_total, sizeof(int64_t), hipHostMallocDefault));
   int64_t *row_bytes = w.rows, *row_off = w.rows + w.cap, *total = w.rows + 2 * (int64_t)w.cap;
-  HIP_TRY(trh::launch_tga_sizes(rgb8, width, height, row_bytes, row_off, total, st));
-  HIP_TRY(hipMemcpyAsync(w.h_total, total, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+  HIP_TRY(trh::launch_tga_sizes(rgb8, width, height, row_bytes, row_off, total, w.h_total, st));
   HIP_TRY(hipStreamSynchronize(st));
   *size = *w.h_total;
   if (*size > capacity)

@@ -96,10 +96,10 @@ hipError_t launch_bvh_boxes(const BuildArgs &a, const BvhScratch &w, int32_t max
 hipError_t launch_quantize_rgb8(const float *in, int64_t n, uint8_t *out, hipStream_t st);
 // Run-length Targa file of an 8-bit RGB image [H][W][3] (1 <= W, H <= 65535):
 // sizes computes row_bytes[H], row_off[H] (absolute file offsets of the rows)
-// and *total (the file size); write then fills out[0, *total), which must
+// and *total (the file size, also to pinned host memory); write then fills out[0, *total), which must
 // hold *total bytes.
 hipError_t launch_tga_sizes(const uint8_t *rgb, int32_t W, int32_t H, int64_t *row_bytes,
-                            int64_t *row_off, int64_t *total, hipStream_t st);
+                            int64_t *row_off, int64_t *total, int64_t *h_total, hipStream_t st);
 hipError_t launch_tga_write(const uint8_t *rgb, int32_t W, int32_t H, const int64_t *row_off,
                             const int64_t *total, uint8_t *out, hipStream_t st);
 // rgb[i] = (rgb[i] + planes[0][i] + ... + planes[n_planes - 1][i]) / (n_planes + 1),
