@@ -6,6 +6,8 @@
 // Compiled with -ffp-contract=off: the cell lists must equal, bit for bit,
 // those of the grid definition (primitive boxes widened by delta, spheres
 // kept only where their centre lies within r of the widened cell box).
+#include <algorithm>
+
 #include "tr_internal.h"
 
 namespace {
@@ -149,17 +151,17 @@ __global__ void k_pack(const trh::PackArgs P) {
 // distance plus its radius, a cylinder's farther end plus its radius, a
 // triangle's farthest vertex), in FP64, as the bit pattern of a non-negative
 // double (whose order is the integer order of its bits) maxed into *rmax64
-// (zero on entry): one atomic per wave.
+// (zero on entry): one atomic per workgroup.
 __device__ __forceinline__ double dist3(double x, double y, double z) {
   return sqrt((x * x + y * y) + z * z);
 }
 
-__global__ void k_pack32(const trh::BuildArgs a, const double4 *cylW64, double ox, double oy,
-                         double oz, float4 *sph32, float4 *cylA32, float4 *cylW32, float4 *triV32,
-                         float4 *triE1_32, float4 *triE2_32, unsigned long long *rmax64) {
+__device__ __forceinline__ void pack32(const trh::BuildArgs &a, const trh::Pack32Args &P, int64_t k) {
   const int64_t n_s = a.n_s, n_c = a.n_c;
-  const double4 *sph64 = a.sph64, *cylA64 = a.cylA64, *cylB64 = a.cylB64;
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const double4 *sph64 = a.sph64, *cylA64 = a.cylA64, *cylB64 = a.cylB64, *cylW64 = P.cylW64;
+  float4 *sph32 = P.sph32, *cylA32 = P.cylA32, *cylW32 = P.cylW32;
+  float4 *triV32 = P.triV32, *triE1_32 = P.triE1_32, *triE2_32 = P.triE2_32;
+  const double ox = P.origin[0], oy = P.origin[1], oz = P.origin[2];
   double ext = 0.0;  // this primitive's farthest point from the centre
   if (k >= n_s + n_c && k < n_s + n_c + a.n_t) {
     // triangle: v0 in the FP32 frame, its edges (differences taken in FP64),
@@ -198,10 +200,15 @@ __global__ void k_pack32(const trh::BuildArgs a, const double4 *cylW64, double o
                            (float)(0.5 * (a.z + b.z) - oz), nextafterf(bb, INFINITY));
     ext = fmax(dist3(a.x - ox, a.y - oy, a.z - oz), dist3(b.x - ox, b.y - oy, b.z - oz)) + a.w;
   }
-  // every lane gets here (no early return): the wave's maximum, one atomic
+  // every thread gets here (no early return): the workgroup's maximum
+  __shared__ double wave_ext[kBlock / 64];
   for (int off = 32; off > 0; off >>= 1) ext = fmax(ext, __shfl_xor(ext, off, 64));
-  if ((threadIdx.x & 63) == 0 && ext > 0.0)
-    atomicMax(rmax64, (unsigned long long)__double_as_longlong(ext));
+  if ((threadIdx.x & 63) == 0) wave_ext[threadIdx.x >> 6] = ext;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int q = 1; q < kBlock / 64; ++q) ext = fmax(ext, wave_ext[q]);
+    if (ext > 0.0) atomicMax(P.rmax64, (unsigned long long)__double_as_longlong(ext));
+  }
 }
 
 // Per-block min/max of primitive boxes -> scratch[block*6 .. +6].
@@ -277,30 +284,40 @@ __global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v) {
     p[i] = v;
 }
 
-// Per-cell counts, and the reference total summed in 64 bits (total64, zero
-// on entry): the 32-bit counts are exact (a cell holds fewer than 2^28
-// primitives), but their sum may pass 2^32, which the scan would wrap; the
-// host reads total64 and refuses the grid before the scatter.
-__global__ __launch_bounds__(kBlock) void k_count(trh::BuildArgs a, uint32_t *count,
-                                                  unsigned long long *total64) {
-  __shared__ unsigned long long blk;
-  if (threadIdx.x == 0) blk = 0ull;
-  __syncthreads();
+// Zero the per-cell counts (and the two words of total64).
+__global__ void k_grid_init(uint32_t *count, int64_t n, unsigned long long *total64) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t k = t / kLanes;
-  unsigned long long mine = 0ull;
-  if (k < (int64_t)a.n_s + a.n_c + a.n_t)
-    for_prim_cells(a, k, (int)(t % kLanes), [&](uint32_t c) {
-      atomicAdd(&count[c], 1u);
-      ++mine;
-    });
-  if (mine) atomicAdd(&blk, mine);
-  __syncthreads();
-  if (threadIdx.x == 0 && blk) atomicAdd(total64, blk);
+  for (int64_t i = t; i < n; i += (int64_t)gridDim.x * blockDim.x) count[i] = 0u;
+  if (t < 2) total64[t] = 0ull;
+}
+
+// Per-cell counts (workgroups below n_count) and the FP32 copies (the rest):
+// both need only the grid's parameters, so they share a launch.  The
+// references are totalled by the scan: an atomic per workgroup on one word,
+// 7 ns each, was half of the counting of 10^6 objects (810 us).
+__global__ __launch_bounds__(kBlock) void k_count_pack(const trh::BuildArgs a, const trh::Pack32Args P,
+                                                       uint32_t n_count, uint32_t *count) {
+  if (blockIdx.x < n_count) {
+    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t k = t / kLanes;
+    if (k < (int64_t)a.n_s + a.n_c + a.n_t)
+      for_prim_cells(a, k, (int)(t % kLanes), [&](uint32_t c) { atomicAdd(&count[c], 1u); });
+  } else {
+    pack32(a, P, (int64_t)(blockIdx.x - n_count) * kBlock + threadIdx.x);
+  }
+}
+
+// Whether the references and the walk lists fit their buffers: the kernels
+// after the scan are launched before the host has read the total, and leave
+// everything alone when it does not fit (the host then grows the buffers and
+// launches them again).
+__device__ __forceinline__ bool fits(const unsigned long long *total64, unsigned long long cap) {
+  return total64[0] <= cap;
 }
 
 __global__ void k_scatter(trh::BuildArgs a, const uint32_t *cell_begin, uint32_t *cursor,
-                          uint32_t *refs) {
+                          uint32_t *refs, const unsigned long long *total64, unsigned long long cap) {
+  if (!fits(total64, cap)) return;
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t k = t / kLanes;
   if (k >= (int64_t)a.n_s + a.n_c + a.n_t) return;
@@ -320,12 +337,26 @@ __global__ void k_scatter(trh::BuildArgs a, const uint32_t *cell_begin, uint32_t
 // the length of its own list, so the long lists of dense regions do not hold
 // a wave back the way a per-cell sort does.  A block whose range exceeds the
 // stage sorts in place in global memory instead (same result).
+//
+// The FP32 walk's view of the occupied cells is written on the way: each
+// reference also goes to its place in the cell's walk list (whose offset the
+// scan left in the cell's record), as its record offset, 16 x its id (the
+// byte offset of its 16-byte FP32 records), with bit 0 set on a list's last
+// entry; -1 ends the list, and the cell's record gets the list's first entry.
+// One 8-byte load gives the walk the cell's first unit of work, and it knows
+// a cell's last test when it makes it.  (The host keeps ids below 2^27 and
+// the lists below 2^29 words, so both fit a signed 32-bit word.)
 constexpr int kSortStage = 8192;  // refs per block staged in LDS (32 KiB)
 
 __global__ __launch_bounds__(kBlock) void k_sort_cells(const uint32_t *cell_begin, int64_t n_cells,
-                                                       uint32_t *refs) {
+                                                       uint32_t *refs, uint32_t *wrefs,
+                                                       trd::CellInfo *info,
+                                                       const unsigned long long *total64,
+                                                       unsigned long long cap) {
+  if (!fits(total64, cap)) return;
   __shared__ uint32_t stage[kSortStage];
   __shared__ uint32_t offs[kBlock + 1];
+  __shared__ uint32_t woffs[kBlock];  // walk lists
   const int64_t c0 = (int64_t)blockIdx.x * kBlock;
   const int64_t c = c0 + threadIdx.x;
   const int nb = (int)min((int64_t)kBlock, n_cells - c0);  // cells in this block
@@ -334,6 +365,7 @@ __global__ __launch_bounds__(kBlock) void k_sort_cells(const uint32_t *cell_begi
   if (n <= (uint32_t)kSortStage) {
     for (uint32_t i = threadIdx.x; i < n; i += kBlock) stage[i] = refs[r0 + i];
     for (int i = threadIdx.x; i <= nb; i += kBlock) offs[i] = cell_begin[c0 + i] - r0;
+    if ((int)threadIdx.x < nb) woffs[threadIdx.x] = (uint32_t)info[c].a >> 2;  // (read only if occupied)
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < n; i += kBlock) {
       // last k with offs[k] <= i; offs[0] = 0 <= i < n = offs[nb]
@@ -347,6 +379,10 @@ __global__ __launch_bounds__(kBlock) void k_sort_cells(const uint32_t *cell_begi
       uint32_t rank = 0;
       for (uint32_t j = b; j < e; ++j) rank += stage[j] < v ? 1u : 0u;
       refs[r0 + b + rank] = v;
+      const uint32_t entry = (v << 4) | (rank + 1 == e - b ? 1u : 0u);
+      wrefs[woffs[lo] + rank] = entry;
+      if (rank + 1 == e - b) wrefs[woffs[lo] + rank + 1] = 0xFFFFFFFFu;
+      if (rank == 0) info[c0 + lo].c = (int32_t)entry;
     }
   } else if (c < n_cells) {
     const uint32_t b = cell_begin[c], e = cell_begin[c + 1];
@@ -359,6 +395,12 @@ __global__ __launch_bounds__(kBlock) void k_sort_cells(const uint32_t *cell_begi
       }
       refs[j] = v;
     }
+    if (e > b) {
+      const uint32_t w = (uint32_t)info[c].a >> 2;
+      for (uint32_t i = b; i < e; ++i) wrefs[w + (i - b)] = (refs[i] << 4) | (i + 1 == e ? 1u : 0u);
+      wrefs[w + (e - b)] = 0xFFFFFFFFu;
+      info[c].c = (int32_t)((refs[b] << 4) | (e - b == 1 ? 1u : 0u));
+    }
   }
 }
 
@@ -370,12 +412,6 @@ __global__ __launch_bounds__(kBlock) void k_sort_cells(const uint32_t *cell_begi
 // distance is the min over occupied y of max over axes of |x_a - y_a|, and
 // max distributes over min, so the axes can be taken one at a time.
 constexpr int kDistCap = 32;
-
-__global__ void k_dist_init(const uint32_t *cell_begin, int64_t n_cells, uint8_t *d, int32_t cap) {
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= n_cells) return;
-  d[c] = cell_begin[c + 1] > cell_begin[c] ? 0 : (uint8_t)cap;
-}
 
 __global__ void k_dist_pass(const uint8_t *in, uint8_t *out, int32_t rx, int32_t ry, int32_t rz,
                             int axis, int32_t cap) {
@@ -398,73 +434,179 @@ __global__ void k_dist_pass(const uint8_t *in, uint8_t *out, int32_t rx, int32_t
   out[c] = (uint8_t)best;
 }
 
-// Walk-list sizes: an occupied cell's references plus one end marker (the
-// extra last entry is 0, so the exclusive scan leaves the total there).
-__global__ void k_walk_sizes(const uint32_t *cell_begin, int64_t n_cells, uint32_t *w) {
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c > n_cells) return;
-  const uint32_t n = c < n_cells ? cell_begin[c + 1] - cell_begin[c] : 0u;
-  w[c] = n ? n + 1u : 0u;
-}
-
-// Traversal view of a cell, after the scan of the walk-list sizes: an
-// occupied cell copies its sorted references to its walk list, appends -1,
-// and records (byte offset of the list, first entry); an empty cell records
-// (-distance, -1).  One 8-byte load gives the walk the cell's first unit of
-// work, and the end marker ends the list without an end index.  The lists
-// hold each primitive as its record offset, 16 x its id (the byte offset of
-// its 16-byte FP32 records), with bit 0 set on a list's last entry, and the
-// walk moves through them by byte offset: neither needs a multiply on the
-// walk, and the walk knows a cell's last test when it makes it.  (The host keeps ids below 2^27 and
-// the lists below 2^29 words, so both fit a signed 32-bit word.)
-__global__ void k_cellinfo(const uint32_t *cell_begin, const uint32_t *refs, const uint32_t *wbegin,
-                           const uint8_t *d, int64_t n_cells, int32_t rx, int32_t ry, int32_t cap,
-                           uint32_t *wrefs, trd::CellInfo *info) {
+// Records of the empty cells: (-distance, bit 31 and the empty blocks ahead).
+// dc is the cell's Chebyshev distance (the cube of half-size dc - 1 about it is
+// empty); the blocks are those ahead of it, per octant of a ray's direction.
+// From the cell, the block of side 2m + 1 that extends ahead in octant o (axis
+// a towards -a where bit a of o is set) is the cube of half-size m about the
+// cell m steps along that octant's diagonal, so it is empty when that cell's
+// distance is at least m + 1.  Such blocks grow with m while the condition
+// holds; the record keeps the largest m, M <= 7 (and 2M + 1 within the cap),
+// in three bits per octant, and a ray in that octant jumps max(dc, 2M + 1)
+// cells ahead.  (The walk is clamped to the part of the cube ahead of it, so a
+// block that is empty ahead of the cell is enough.)  The scan stays inside the
+// grid.  Bound by the latency of its byte loads: the eight octants' loads of a
+// step go out together (one octant after the other, each step's load waited
+// for the one before).
+__global__ __launch_bounds__(kBlock) void k_empty_cells(const uint8_t *d, int64_t n_cells, int32_t rx,
+                                                        int32_t ry, int32_t rz, int32_t cap,
+                                                        trd::CellInfo *info) {
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= n_cells) return;
-  const uint32_t b = cell_begin[c], e = cell_begin[c + 1];
-  trd::CellInfo r;
-  if (b < e) {
-    const uint32_t w = wbegin[c];
-    // bit 0 (free: record offsets are multiples of 16) flags a list's last entry
-    for (uint32_t i = 0; i < e - b; ++i) wrefs[w + i] = (refs[b + i] << 4) | (i + 1 == e - b ? 1u : 0u);
-    wrefs[w + (e - b)] = 0xFFFFFFFFu;
-    r.a = (int32_t)(w << 2);
-    r.c = (int32_t)((refs[b] << 4) | (e - b == 1 ? 1u : 0u));
-  } else {
-    // An empty cell: its Chebyshev distance dc (the cube of half-size dc - 1
-    // about it is empty), and per octant of a ray's direction the block
-    // ahead of it that is empty.  From the cell, the block of side 2m + 1
-    // that extends ahead in octant o (axis a towards -a where bit a of o is
-    // set) is the cube of half-size m about the cell m steps along that
-    // octant's diagonal, so it is empty when that cell's distance is at
-    // least m + 1.  Such blocks grow with m while the condition holds; the
-    // record keeps the largest m, M <= 7 (and 2M + 1 within the cap), in
-    // three bits per octant, and a ray in that octant jumps max(dc, 2M + 1)
-    // cells ahead.  (The walk is clamped to the part of the cube ahead of
-    // it, so a block that is empty ahead of the cell is enough.)  The scan
-    // stays inside the grid.
-    const int32_t dc = max((int32_t)d[c], 1);
-    const int32_t ix = (int32_t)(c % rx), iy = (int32_t)((c / rx) % ry),
-                  iz = (int32_t)(c / ((int64_t)rx * ry));
-    const int32_t rz = (int32_t)(n_cells / ((int64_t)rx * ry));
-    const int32_t mcap = min(7, (cap - 1) / 2);
-    uint32_t ext = 0;
-    for (int32_t o = 0; o < 8; ++o) {
-      const int32_t sx = (o & 1) ? -1 : 1, sy = (o & 2) ? -1 : 1, sz = (o & 4) ? -1 : 1;
-      int32_t m = 0;
-      while (m < mcap) {
-        const int32_t jx = ix + (m + 1) * sx, jy = iy + (m + 1) * sy, jz = iz + (m + 1) * sz;
-        if (jx < 0 || jx >= rx || jy < 0 || jy >= ry || jz < 0 || jz >= rz) break;
-        if ((int32_t)d[((int64_t)jz * ry + jy) * rx + jx] < m + 2) break;
-        ++m;
-      }
-      ext |= (uint32_t)m << (3 * o);
+  const int32_t dc = (int32_t)d[c];
+  if (dc == 0) return;  // occupied
+  const int32_t row = (int32_t)c / rx;  // (a grid has at most 512^3 cells)
+  const int32_t ix = (int32_t)c - row * rx, iz = row / ry, iy = row - iz * ry;
+  const int32_t mcap = min(7, (cap - 1) / 2);
+  uint32_t ext = 0, open = 0xFFu;  // open: octants still growing
+  for (int32_t m = 1; m <= mcap && open; ++m) {
+    // octants whose diagonal leaves the grid
+    uint32_t out = 0;
+    if (ix + m >= rx) out |= 0x55u;
+    if (ix - m < 0) out |= 0xAAu;
+    if (iy + m >= ry) out |= 0x33u;
+    if (iy - m < 0) out |= 0xCCu;
+    if (iz + m >= rz) out |= 0x0Fu;
+    if (iz - m < 0) out |= 0xF0u;
+    open &= ~out;
+    const int32_t sy = m * rx, sz = m * rx * ry;
+    int32_t v[8];
+#pragma unroll
+    for (int o = 0; o < 8; ++o) {
+      const int32_t at = (int32_t)c + ((o & 1) ? -m : m) + ((o & 2) ? -sy : sy) + ((o & 4) ? -sz : sz);
+      v[o] = d[((open >> o) & 1u) ? at : (int32_t)c];
     }
-    r.a = -dc;
-    r.c = (int32_t)(0x80000000u | ext);
+#pragma unroll
+    for (int o = 0; o < 8; ++o) {
+      if (((open >> o) & 1u) && v[o] >= m + 1) ext += 1u << (3 * o);
+      else open &= ~(1u << o);
+    }
   }
+  trd::CellInfo r;
+  r.a = -dc;
+  r.c = (int32_t)(0x80000000u | ext);
   info[c] = r;
+}
+
+// ---- the cells' scan: references and walk-list words (a cell's references
+// plus one end marker, none for an empty cell) before each cell.  Two
+// launches: totals of 4096 cells each, then every workgroup adds up the totals
+// before its own and scans its cells.  The second also leaves what the next
+// kernels want of a cell: its count zeroed (the scatter's cursor), its
+// distance field started (0 or cap) and an occupied cell's list offset.
+constexpr int kCellsPer = 16;                      // cells per thread, consecutive
+constexpr int kCellsBlock = kBlock * kCellsPer;    // cells per workgroup
+struct CellSums {
+  unsigned long long refs;  // (64 bits: overlapping large primitives pass 2^32)
+  unsigned long long occupied;
+};
+
+__device__ __forceinline__ CellSums block_sum(CellSums v) {
+  __shared__ CellSums part[kBlock / 64];
+  for (int o = 32; o > 0; o >>= 1) {
+    v.refs += __shfl_xor(v.refs, o, 64);
+    v.occupied += __shfl_xor(v.occupied, o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+  __syncthreads();
+  v = part[0];
+  for (int q = 1; q < kBlock / 64; ++q) {
+    v.refs += part[q].refs;
+    v.occupied += part[q].occupied;
+  }
+  __syncthreads();
+  return v;
+}
+
+__global__ __launch_bounds__(kBlock) void k_cell_sums(const uint32_t *count, int64_t n_cells,
+                                                      CellSums *sums) {
+  const int64_t base = (int64_t)blockIdx.x * kCellsBlock;
+  CellSums v{0ull, 0ull};
+#pragma unroll
+  for (int q = 0; q < kCellsPer; ++q) {
+    const int64_t c = base + q * kBlock + threadIdx.x;
+    const uint32_t n = c < n_cells ? count[c] : 0u;
+    v.refs += n;
+    v.occupied += n ? 1u : 0u;
+  }
+  v = block_sum(v);
+  if (threadIdx.x == 0) sums[blockIdx.x] = v;
+}
+
+__global__ __launch_bounds__(kBlock) void k_cell_scan(uint32_t *count, int64_t n_cells,
+                                                      const CellSums *sums, uint32_t cap,
+                                                      uint32_t *cell_begin, uint8_t *d,
+                                                      trd::CellInfo *info,
+                                                      unsigned long long *total64,
+                                                      unsigned long long *h_total) {
+  __shared__ uint32_t stage[kCellsBlock];  // counts, then each cell's references before it
+  __shared__ uint32_t wref[kBlock / 64], wocc[kBlock / 64];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int64_t base = (int64_t)blockIdx.x * kCellsBlock;
+  CellSums b{0ull, 0ull};
+  for (int32_t i = t; i < (int32_t)blockIdx.x; i += kBlock) {
+    b.refs += sums[i].refs;
+    b.occupied += sums[i].occupied;
+  }
+  b = block_sum(b);
+  if (blockIdx.x == gridDim.x - 1 && t == 0) {  // the totals
+    const unsigned long long R = b.refs + sums[blockIdx.x].refs;
+    cell_begin[n_cells] = (uint32_t)R;
+    count[n_cells] = (uint32_t)(R + b.occupied + sums[blockIdx.x].occupied);  // walk-list words
+    total64[0] = R;
+    h_total[0] = R;
+    h_total[1] = total64[1];
+  }
+#pragma unroll
+  for (int q = 0; q < kCellsPer; ++q) {
+    const int64_t c = base + q * kBlock + t;
+    stage[q * kBlock + t] = c < n_cells ? count[c] : 0u;
+  }
+  __syncthreads();
+  uint32_t n[kCellsPer], refs = 0, occ = 0;
+#pragma unroll
+  for (int q = 0; q < kCellsPer; ++q) {
+    n[q] = stage[t * kCellsPer + q];
+    refs += n[q];
+    occ += n[q] ? 1u : 0u;
+  }
+  uint32_t ir = refs, io = occ;  // inclusive over the wave
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t vr = __shfl_up(ir, o, 64), vo = __shfl_up(io, o, 64);
+    if (lane >= o) {
+      ir += vr;
+      io += vo;
+    }
+  }
+  if (lane == 63) {
+    wref[wv] = ir;
+    wocc[wv] = io;
+  }
+  __syncthreads();
+  uint32_t r = (uint32_t)b.refs + ir - refs, w = (uint32_t)b.occupied + io - occ;
+  for (int q = 0; q < wv; ++q) {
+    r += wref[q];
+    w += wocc[q];
+  }
+  w += r;
+#pragma unroll
+  for (int q = 0; q < kCellsPer; ++q) {
+    const int64_t c = base + t * kCellsPer + q;
+    if (n[q] && c < n_cells) info[c].a = (int32_t)(w << 2);
+    stage[t * kCellsPer + q] = r;
+    r += n[q];
+    w += n[q] ? n[q] + 1u : 0u;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kCellsPer; ++q) {  // (count and d in the order of the first loop: coalesced)
+    const int64_t c = base + q * kBlock + t;
+    if (c < n_cells) {
+      cell_begin[c] = stage[q * kBlock + t];
+      d[c] = count[c] ? 0 : (uint8_t)cap;
+      count[c] = 0u;
+    }
+  }
 }
 
 // ---- exclusive scan: blocks of kScanItems, block sums scanned recursively
@@ -780,19 +922,8 @@ hipError_t launch_pack(const PackArgs &p, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_pack32(const BuildArgs &a, const double4 *cylW64, const double origin[3],
-                         float4 *sph32, float4 *cylA32, float4 *cylW32, float4 *triV32,
-                         float4 *triE1_32, float4 *triE2_32, unsigned long long *rmax64,
-                         hipStream_t st) {
-  const int64_t N = (int64_t)a.n_s + a.n_c + a.n_t;
-  if (N == 0) return hipSuccess;
-  k_pack32<<<blocks_for(N), kBlock, 0, st>>>(a, cylW64, origin[0], origin[1], origin[2], sph32,
-                                             cylA32, cylW32, triV32, triE1_32, triE2_32, rmax64);
-  return hipGetLastError();
-}
-
 static int32_t bounds_blocks(int64_t N) {
-  int64_t b = (N + kBlock * 8 - 1) / (kBlock * 8);
+  int64_t b = (N + kBlock - 1) / kBlock;
   if (b < 1) b = 1;
   if (b > 1024) b = 1024;
   return (int32_t)b;
@@ -815,11 +946,30 @@ hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_count(const BuildArgs &a, uint32_t *count, unsigned long long *total64,
-                        hipStream_t st) {
+hipError_t launch_count_pack(const BuildArgs &a, const Pack32Args &p, uint32_t *count, int64_t n_cells,
+                             unsigned long long *total64, hipStream_t st) {
   const int64_t N = (int64_t)a.n_s + a.n_c + a.n_t;
-  if (N == 0) return hipSuccess;
-  k_count<<<blocks_for(N * kLanes), kBlock, 0, st>>>(a, count, total64);
+  k_grid_init<<<(unsigned)std::min<int64_t>(blocks_for(n_cells + 1), 65536), kBlock, 0, st>>>(
+      count, n_cells + 1, total64);
+  if (N > 0) {
+    const unsigned nc = blocks_for(N * kLanes);
+    k_count_pack<<<nc + blocks_for(N), kBlock, 0, st>>>(a, p, nc, count);
+  }
+  return hipGetLastError();
+}
+
+int64_t cell_scan_words(int64_t n_cells) {
+  return (n_cells + kCellsBlock - 1) / kCellsBlock * (int64_t)(sizeof(CellSums) / 4);
+}
+
+hipError_t launch_cell_scan(uint32_t *count, int64_t n_cells, int32_t cap, uint32_t *scratch,
+                            uint32_t *cell_begin, uint8_t *d0, trd::CellInfo *info,
+                            unsigned long long *total64, unsigned long long *h_total, hipStream_t st) {
+  const unsigned nb = (unsigned)((n_cells + kCellsBlock - 1) / kCellsBlock);
+  if (cap < 1 || cap > kDistCap) cap = kDistCap;
+  k_cell_sums<<<nb, kBlock, 0, st>>>(count, n_cells, (CellSums *)scratch);
+  k_cell_scan<<<nb, kBlock, 0, st>>>(count, n_cells, (const CellSums *)scratch, (uint32_t)cap, cell_begin,
+                                     d0, info, total64, h_total);
   return hipGetLastError();
 }
 
@@ -849,11 +999,15 @@ hipError_t launch_scan(uint32_t *data, int64_t n, uint32_t *scratch, hipStream_t
   return hipGetLastError();
 }
 
-hipError_t launch_scatter(const BuildArgs &a, const uint32_t *cell_begin, uint32_t *cursor,
-                          uint32_t *refs, hipStream_t st) {
+hipError_t launch_lists(const BuildArgs &a, const uint32_t *cell_begin, int64_t n_cells, uint32_t *cursor,
+                        uint32_t *refs, uint32_t *wrefs, trd::CellInfo *info,
+                        const unsigned long long *total64, int64_t cap, hipStream_t st) {
   const int64_t N = (int64_t)a.n_s + a.n_c + a.n_t;
   if (N == 0) return hipSuccess;
-  k_scatter<<<blocks_for(N * kLanes), kBlock, 0, st>>>(a, cell_begin, cursor, refs);
+  k_scatter<<<blocks_for(N * kLanes), kBlock, 0, st>>>(a, cell_begin, cursor, refs, total64,
+                                                       (unsigned long long)cap);
+  k_sort_cells<<<blocks_for(n_cells), kBlock, 0, st>>>(cell_begin, n_cells, refs, wrefs, info, total64,
+                                                       (unsigned long long)cap);
   return hipGetLastError();
 }
 
@@ -914,31 +1068,16 @@ hipError_t launch_bvh_boxes(const BuildArgs &a, const BvhScratch &w, int32_t max
   return hipGetLastError();
 }
 
-hipError_t launch_sort_cells(const uint32_t *cell_begin, int64_t n_cells, uint32_t *refs,
-                             hipStream_t st) {
-  if (n_cells <= 0) return hipSuccess;
-  k_sort_cells<<<(unsigned)((n_cells + kBlock - 1) / kBlock), kBlock, 0, st>>>(cell_begin, n_cells, refs);
-  return hipGetLastError();
-}
-
-hipError_t launch_cellinfo(const uint32_t *cell_begin, const uint32_t *refs, const int32_t res[3],
-                           int32_t cap, uint8_t *d0, uint8_t *d1, uint32_t *wsz,
-                           uint32_t *scan_scratch, uint32_t *wrefs, trd::CellInfo *info,
-                           hipStream_t st) {
+hipError_t launch_empty_cells(const int32_t res[3], int32_t cap, uint8_t *d0, uint8_t *d1,
+                              trd::CellInfo *info, hipStream_t st) {
   const int64_t n = (int64_t)res[0] * res[1] * res[2];
   if (n <= 0) return hipSuccess;
   const unsigned nb = blocks_for(n);
   if (cap < 1 || cap > kDistCap) cap = kDistCap;
-  k_dist_init<<<nb, kBlock, 0, st>>>(cell_begin, n, d0, cap);
   k_dist_pass<<<nb, kBlock, 0, st>>>(d0, d1, res[0], res[1], res[2], 0, cap);
   k_dist_pass<<<nb, kBlock, 0, st>>>(d1, d0, res[0], res[1], res[2], 1, cap);
   k_dist_pass<<<nb, kBlock, 0, st>>>(d0, d1, res[0], res[1], res[2], 2, cap);
-  k_walk_sizes<<<blocks_for(n + 1), kBlock, 0, st>>>(cell_begin, n, wsz);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  e = launch_scan(wsz, n + 1, scan_scratch, st);
-  if (e != hipSuccess) return e;
-  k_cellinfo<<<nb, kBlock, 0, st>>>(cell_begin, refs, wsz, d1, n, res[0], res[1], cap, wrefs, info);
+  k_empty_cells<<<nb, kBlock, 0, st>>>(d1, n, res[0], res[1], res[2], cap, info);
   return hipGetLastError();
 }
 

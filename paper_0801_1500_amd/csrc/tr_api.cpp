@@ -79,6 +79,7 @@ struct tr_scene {
   size_t bytes_arrays = 0;
   // pinned readback
   double *h_bounds = nullptr;
+  hipEvent_t counted = nullptr;  // the reference total is in h_total
   unsigned long long *h_total = nullptr;
   trh::GridParams gp{};
   int64_t n_refs = 0;
@@ -100,6 +101,7 @@ static void free_scene_arrays(tr_scene *s) {
                   s->bvh_nodes, s->total64};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
+  if (s->counted) (void)hipEventDestroy(s->counted);
   if (s->h_bounds) (void)hipHostFree(s->h_bounds);
   if (s->h_total) (void)hipHostFree(s->h_total);
 }
@@ -221,10 +223,6 @@ static tr_status build_grid_impl(tr_scene *s, hipStream_t st) {
     grid_params(s->h_bounds, s->h_bounds + 3, N, s->lambda, s->gp);
   }
   for (int a = 0; a < 3; ++a) s->org[a] = 0.5 * (s->gp.lo[a] + s->gp.hi[a]);
-  // reference total and bounding radius, both read back after the count pass
-  HIP_TRY(trh::launch_fill_u32((uint32_t *)s->total64, 4, 0u, st));
-  HIP_TRY(trh::launch_pack32(a, s->cylW64, s->org, s->sph32, s->cylA32, s->cylW32, s->triV32,
-                             s->triE1_32, s->triE2_32, s->total64 + 1, st));
   const int64_t nc = s->gp.n_cells;
   if (nc + 1 > s->cap_cells) {
     if (s->cell_begin) (void)hipFree(s->cell_begin);
@@ -242,7 +240,7 @@ static tr_status build_grid_impl(tr_scene *s, hipStream_t st) {
     HIP_TRY(dmalloc(&s->dist1, nc + 1));
     s->cap_cells = nc + 1;
   }
-  const int64_t need_scan = trh::scan_scratch_u32(nc + 1);
+  const int64_t need_scan = trh::cell_scan_words(nc);
   if (need_scan > s->cap_scan) {
     if (s->scan_scratch) (void)hipFree(s->scan_scratch);
     s->scan_scratch = nullptr;
@@ -256,15 +254,38 @@ static tr_status build_grid_impl(tr_scene *s, hipStream_t st) {
     a.res[q] = s->gp.res[q];
   }
   a.delta = s->gp.delta;
-  HIP_TRY(trh::launch_fill_u32(s->cell_begin, nc + 1, 0u, st));
-  HIP_TRY(trh::launch_count(a, s->cell_begin, s->total64, st));
-  HIP_TRY(hipMemcpyAsync(s->h_total, s->total64, 2 * sizeof(*s->h_total), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
+  trh::Pack32Args p32{};
+  p32.cylW64 = s->cylW64;
+  for (int q = 0; q < 3; ++q) p32.origin[q] = s->org[q];
+  p32.sph32 = s->sph32;
+  p32.cylA32 = s->cylA32;
+  p32.cylW32 = s->cylW32;
+  p32.triV32 = s->triV32;
+  p32.triE1_32 = s->triE1_32;
+  p32.triE2_32 = s->triE2_32;
+  p32.rmax64 = s->total64 + 1;
+  if (!s->counted) HIP_TRY(hipEventCreateWithFlags(&s->counted, hipEventDisableTiming));
+  HIP_TRY(trh::launch_count_pack(a, p32, s->count, nc, s->total64, st));
+  HIP_TRY(trh::launch_cell_scan(s->count, nc, s->max_skip, s->scan_scratch, s->cell_begin, s->dist0,
+                                s->cellinfo, s->total64, s->h_total, st));
+  HIP_TRY(hipEventRecord(s->counted, st));
+  // The rest is enqueued before the host reads the reference total, so the GPU
+  // does not wait for it: the lists are left alone where they would not fit
+  // the buffers (a rebuild's fit, unless it asks for a finer grid), and are
+  // launched again once these have grown.
+  const auto cap_lists = [&]() { return std::min(s->cap_refs, s->cap_wrefs - (nc + 1)); };
+  const auto lists = [&]() {
+    return trh::launch_lists(a, s->cell_begin, nc, s->count, s->refs, s->wrefs, s->cellinfo, s->total64,
+                             cap_lists(), st);
+  };
+  const bool early = cap_lists() > 0;
+  if (early) HIP_TRY(lists());
+  HIP_TRY(trh::launch_empty_cells(s->gp.res, s->max_skip, s->dist0, s->dist1, s->cellinfo, st));
+  HIP_TRY(hipEventSynchronize(s->counted));
   // The total is summed in 64 bits: overlapping large primitives can list
-  // more than 2^32 references, which the 32-bit scan would wrap.  Walk lists
+  // more than 2^32 references, which the 32-bit scan wraps.  Walk lists
   // (references plus one end marker per occupied cell) are addressed with
-  // signed 32-bit byte offsets by the traversal, so the limit is checked
-  // before the scan and the scatter run.
+  // signed 32-bit byte offsets by the traversal.
   const unsigned long long R64 = s->h_total[0];
   std::memcpy(&s->rbound, s->h_total + 1, sizeof(double));  // (0 for an empty scene)
   if (R64 + (unsigned long long)nc + 1ull > (1ull << 29))
@@ -273,25 +294,23 @@ static tr_status build_grid_impl(tr_scene *s, hipStream_t st) {
                 R64, (long long)nc);
   const int64_t R = (int64_t)R64;
   const int64_t W = R + nc + 1;  // bound on the walk-list total
-  HIP_TRY(trh::launch_scan(s->cell_begin, nc + 1, s->scan_scratch, st));
+  const bool fit = early && R <= cap_lists();
   if (R > s->cap_refs) {
     if (s->refs) (void)hipFree(s->refs);
     s->refs = nullptr;
+    s->cap_refs = 0;
     HIP_TRY(dmalloc(&s->refs, R));
     s->cap_refs = R;
   }
   if (W > s->cap_wrefs) {
     if (s->wrefs) (void)hipFree(s->wrefs);
     s->wrefs = nullptr;
+    s->cap_wrefs = 0;
     HIP_TRY(dmalloc(&s->wrefs, W));
     s->cap_wrefs = W;
   }
   s->n_refs = R;
-  HIP_TRY(trh::launch_fill_u32(s->count, nc, 0u, st));
-  HIP_TRY(trh::launch_scatter(a, s->cell_begin, s->count, s->refs, st));
-  HIP_TRY(trh::launch_sort_cells(s->cell_begin, nc, s->refs, st));
-  HIP_TRY(trh::launch_cellinfo(s->cell_begin, s->refs, s->gp.res, s->max_skip, s->dist0, s->dist1,
-                               s->count, s->scan_scratch, s->wrefs, s->cellinfo, st));
+  if (!fit) HIP_TRY(lists());
   fill_scene_dev(s);
   return TR_OK;
 }

@@ -39,33 +39,42 @@ struct PackArgs {
 hipError_t launch_pack(const PackArgs &p, hipStream_t st);
 // FP32 copies with positions relative to origin (the centre of the grid box);
 // also maxes the scene's bounding radius about origin (FP64 bits) into
-// *rmax64, which must be zero on entry
-hipError_t launch_pack32(const BuildArgs &a, const double4 *cylW64, const double origin[3],
-                         float4 *sph32, float4 *cylA32, float4 *cylW32, float4 *triV32,
-                         float4 *triE1_32, float4 *triE2_32, unsigned long long *rmax64,
-                         hipStream_t st);
+// *rmax64
+struct Pack32Args {
+  const double4 *cylW64;
+  double origin[3];
+  float4 *sph32, *cylA32, *cylW32, *triV32, *triE1_32, *triE2_32;
+  unsigned long long *rmax64;
+};
 // bounds: out6 = (lo xyz, hi xyz); scratch >= bounds_scratch_doubles(N) doubles
 int64_t bounds_scratch_doubles(int64_t n_prims);
 hipError_t launch_bounds(const BuildArgs &a, double *scratch, double *out6, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t st);
-// per-cell counts (count zeroed) and their 64-bit total added to *total64 (zeroed)
-hipError_t launch_count(const BuildArgs &a, uint32_t *count, unsigned long long *total64,
-                        hipStream_t st);
+// per-cell counts (count[n_cells + 1] and total64[2] are zeroed first) and the
+// FP32 copies
+hipError_t launch_count_pack(const BuildArgs &a, const Pack32Args &p, uint32_t *count, int64_t n_cells,
+                             unsigned long long *total64, hipStream_t st);
+// exclusive scan of the counts into cell_begin[n_cells + 1]: zeroes the counts
+// (count[n_cells] = walk-list words), starts the distance field d0, leaves the
+// occupied cells' list offsets in info, and the reference total in total64[0]
+// and, with total64[1], in h_total (pinned).  scratch: cell_scan_words words.
+int64_t cell_scan_words(int64_t n_cells);
+hipError_t launch_cell_scan(uint32_t *count, int64_t n_cells, int32_t cap, uint32_t *scratch,
+                            uint32_t *cell_begin, uint8_t *d0, trd::CellInfo *info,
+                            unsigned long long *total64, unsigned long long *h_total, hipStream_t st);
+// reference lists, sorted, and walk lists; nothing is written when the
+// reference total exceeds cap
+hipError_t launch_lists(const BuildArgs &a, const uint32_t *cell_begin, int64_t n_cells, uint32_t *cursor,
+                        uint32_t *refs, uint32_t *wrefs, trd::CellInfo *info,
+                        const unsigned long long *total64, int64_t cap, hipStream_t st);
+// empty-space distances (d0: started by the scan; d1: n_cells bytes) and the
+// records of the empty cells.
+// cap: largest stored distance, 1..32 (1 = no jumps); anything else = 32
+hipError_t launch_empty_cells(const int32_t res[3], int32_t cap, uint8_t *d0, uint8_t *d1,
+                              trd::CellInfo *info, hipStream_t st);
 // exclusive scan of n+1 entries in place (data[n] must be 0 on entry)
 int64_t scan_scratch_u32(int64_t n);
 hipError_t launch_scan(uint32_t *data, int64_t n_plus_1, uint32_t *scratch, hipStream_t st);
-hipError_t launch_scatter(const BuildArgs &a, const uint32_t *cell_begin, uint32_t *cursor,
-                          uint32_t *refs, hipStream_t st);
-// empty-space distance field + per-cell traversal words (d0, d1: n_cells bytes each)
-// Empty-space distances, walk lists (wsz: n_cells + 1 scratch words, scanned
-// in place with scan_scratch) and the per-cell traversal records.
-// cap: largest stored distance, 1..32 (1 = no jumps); anything else = 32
-hipError_t launch_cellinfo(const uint32_t *cell_begin, const uint32_t *refs, const int32_t res[3],
-                           int32_t cap, uint8_t *d0, uint8_t *d1, uint32_t *wsz,
-                           uint32_t *scan_scratch, uint32_t *wrefs, trd::CellInfo *info,
-                           hipStream_t st);
-hipError_t launch_sort_cells(const uint32_t *cell_begin, int64_t n_cells, uint32_t *refs,
-                             hipStream_t st);
 
 // Linear BVH over all primitives (n >= 2): 4 float4 per internal node (see
 // k_bvh_pack); node 0 is the root.  Scratch sizes: keys, vals, keys2, vals2,
