@@ -344,7 +344,9 @@ tr_status tr_scene_walk_arrays(const tr_scene *scene, int32_t *cellinfo, uint32_
                                int64_t *n_walk, void *hip_stream);
 
 /* Free the scene's device memory.  The caller guarantees no enqueued work
- * still uses it (the call synchronises the device before freeing). */
+ * still uses it (the call synchronises the device before freeing).  Up to
+ * 256 MB of freed blocks per device stay with the library for the next scene,
+ * until the device runs out of memory. */
 void tr_scene_destroy(tr_scene *scene);
 
 /* ---------------------------------------------------------------- render */

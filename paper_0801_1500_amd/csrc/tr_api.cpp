@@ -16,6 +16,7 @@
 #include <mutex>
 #include <string>
 #include <tuple>
+#include <unordered_map>
 #include <vector>
 
 #include "tr_internal.h"
@@ -47,6 +48,118 @@ static tr_status fail(tr_status st, const char *fmt, ...) {
 static bool finite3(const double *v) {
   return std::isfinite(v[0]) && std::isfinite(v[1]) && std::isfinite(v[2]);
 }
+
+// --------------------------------------------------------- scene memory
+// Device blocks of freed scenes (and of builds' scratch), kept for the next
+// scene: a protein's scene is some 30 blocks, and taking them from the driver
+// and giving them back cost 0.25 ms of a 0.7 ms build and destroy, 4 ms for
+// 200,000 objects.  Blocks come in sizes of at most one part in eight more than
+// asked for.  At most kKeepBytes a device are kept, all of them are given back
+// when the device runs out of memory, and a block goes back in only once the
+// device is done with it (the caller synchronises first), so any thread may
+// have it on any stream.
+constexpr int kMaxDevices = 64;
+constexpr size_t kKeepBytes = (size_t)256 << 20;
+constexpr size_t kKeepHost = 64;  // pinned blocks
+
+struct KeptBlocks {
+  std::mutex mu;
+  std::multimap<size_t, void *> kept[kMaxDevices];  // by size
+  size_t held[kMaxDevices] = {};
+  std::unordered_map<void *, std::pair<size_t, int>> live;  // size, device
+  std::vector<void *> host;                                 // pinned, kHostBlock bytes each
+};
+static KeptBlocks &blocks() {  // (never destroyed: the driver's own teardown comes first)
+  static KeptBlocks *b = new KeptBlocks();
+  return *b;
+}
+
+static size_t block_size(size_t n) {
+  if (n <= 256) return 256;
+  size_t step = 32;
+  while (step * 16 < n) step *= 2;  // 8 to 16 steps
+  return (n + step - 1) / step * step;
+}
+
+static hipError_t dev_alloc(void **p, size_t bytes) {
+  KeptBlocks &b = blocks();
+  const size_t size = block_size(bytes);
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev >= kMaxDevices) return hipErrorInvalidDevice;
+  std::unique_lock<std::mutex> lk(b.mu);
+  const auto it = b.kept[dev].find(size);
+  if (it != b.kept[dev].end()) {
+    *p = it->second;
+    b.kept[dev].erase(it);
+    b.held[dev] -= size;
+  } else {
+    e = hipMalloc(p, size);
+    if (e == hipErrorOutOfMemory && b.held[dev] > 0) {
+      (void)hipGetLastError();
+      for (const auto &k : b.kept[dev]) (void)hipFree(k.second);
+      b.kept[dev].clear();
+      b.held[dev] = 0;
+      e = hipMalloc(p, size);
+    }
+    if (e != hipSuccess) return e;
+  }
+  b.live[*p] = {size, dev};
+  return hipSuccess;
+}
+
+// The device must be done with the block.
+static void dev_free(void *p) {
+  if (!p) return;
+  KeptBlocks &b = blocks();
+  std::unique_lock<std::mutex> lk(b.mu);
+  const auto it = b.live.find(p);
+  const size_t size = it->second.first;
+  const int dev = it->second.second;
+  b.live.erase(it);
+  if (b.held[dev] + size <= kKeepBytes) {
+    b.kept[dev].emplace(size, p);
+    b.held[dev] += size;
+    return;
+  }
+  lk.unlock();
+  (void)hipFree(p);
+}
+
+constexpr size_t kHostBlock = 128;
+static hipError_t host_alloc(void **p) {
+  KeptBlocks &b = blocks();
+  {
+    std::lock_guard<std::mutex> lk(b.mu);
+    if (!b.host.empty()) {
+      *p = b.host.back();
+      b.host.pop_back();
+      return hipSuccess;
+    }
+  }
+  return hipHostMalloc(p, kHostBlock, hipHostMallocPortable);
+}
+static void host_free(void *p) {
+  if (!p) return;
+  KeptBlocks &b = blocks();
+  {
+    std::lock_guard<std::mutex> lk(b.mu);
+    if (b.host.size() < kKeepHost) {
+      b.host.push_back(p);
+      return;
+    }
+  }
+  (void)hipHostFree(p);
+}
+
+// Pinned staging for the arrays of a scene of up to kStageBytes (26,318
+// objects are 1.8 MB): one copy to the device for its nine to fifteen arrays.
+// One builder at a time has it; others copy array by array.
+constexpr size_t kStageBytes = (size_t)8 << 20;
+static std::mutex g_stage_mu;
+static char *g_stage = nullptr;
+static size_t g_stage_cap = 0;
 
 // ------------------------------------------------------------------ scene
 struct tr_scene {
@@ -99,17 +212,15 @@ static void free_scene_arrays(tr_scene *s) {
                   s->bounds_scratch, s->bounds, s->cellinfo, s->dist0, s->dist1, s->wrefs,
                   s->triA64, s->triB64, s->triC64, s->triV32, s->triE1_32, s->triE2_32,
                   s->bvh_nodes, s->total64};
-  for (void *p : ptrs)
-    if (p) (void)hipFree(p);
+  for (void *p : ptrs) dev_free(p);
   if (s->counted) (void)hipEventDestroy(s->counted);
-  if (s->h_bounds) (void)hipHostFree(s->h_bounds);
-  if (s->h_total) (void)hipHostFree(s->h_total);
+  host_free(s->h_bounds);  // (h_total is in the same block)
 }
 
 template <class T>
 static hipError_t dmalloc(T **p, int64_t n) {
   if (n <= 0) n = 1;
-  return hipMalloc((void **)p, (size_t)n * sizeof(T));
+  return dev_alloc((void **)p, (size_t)n * sizeof(T));
 }
 
 // Grid parameters from the scene bounds (same definition as documented in
@@ -225,14 +336,16 @@ static tr_status build_grid_impl(tr_scene *s, hipStream_t st) {
   for (int a = 0; a < 3; ++a) s->org[a] = 0.5 * (s->gp.lo[a] + s->gp.hi[a]);
   const int64_t nc = s->gp.n_cells;
   if (nc + 1 > s->cap_cells) {
-    if (s->cell_begin) (void)hipFree(s->cell_begin);
-    if (s->count) (void)hipFree(s->count);
-    if (s->cellinfo) (void)hipFree(s->cellinfo);
-    if (s->dist0) (void)hipFree(s->dist0);
-    if (s->dist1) (void)hipFree(s->dist1);
+    if (s->cell_begin) HIP_TRY(hipDeviceSynchronize());  // renders on any stream may read them
+    dev_free(s->cell_begin);
+    dev_free(s->count);
+    dev_free(s->cellinfo);
+    dev_free(s->dist0);
+    dev_free(s->dist1);
     s->cell_begin = s->count = nullptr;
     s->cellinfo = nullptr;
     s->dist0 = s->dist1 = nullptr;
+    s->cap_cells = 0;
     HIP_TRY(dmalloc(&s->cell_begin, nc + 1));
     HIP_TRY(dmalloc(&s->count, nc + 1));
     HIP_TRY(dmalloc(&s->cellinfo, nc + 1));
@@ -242,8 +355,10 @@ static tr_status build_grid_impl(tr_scene *s, hipStream_t st) {
   }
   const int64_t need_scan = trh::cell_scan_words(nc);
   if (need_scan > s->cap_scan) {
-    if (s->scan_scratch) (void)hipFree(s->scan_scratch);
+    if (s->scan_scratch) HIP_TRY(hipDeviceSynchronize());
+    dev_free(s->scan_scratch);
     s->scan_scratch = nullptr;
+    s->cap_scan = 0;
     HIP_TRY(dmalloc(&s->scan_scratch, need_scan));
     s->cap_scan = need_scan;
   }
@@ -296,14 +411,16 @@ static tr_status build_grid_impl(tr_scene *s, hipStream_t st) {
   const int64_t W = R + nc + 1;  // bound on the walk-list total
   const bool fit = early && R <= cap_lists();
   if (R > s->cap_refs) {
-    if (s->refs) (void)hipFree(s->refs);
+    if (s->refs) HIP_TRY(hipDeviceSynchronize());
+    dev_free(s->refs);
     s->refs = nullptr;
     s->cap_refs = 0;
     HIP_TRY(dmalloc(&s->refs, R));
     s->cap_refs = R;
   }
   if (W > s->cap_wrefs) {
-    if (s->wrefs) (void)hipFree(s->wrefs);
+    if (s->wrefs) HIP_TRY(hipDeviceSynchronize());
+    dev_free(s->wrefs);
     s->wrefs = nullptr;
     s->cap_wrefs = 0;
     HIP_TRY(dmalloc(&s->wrefs, W));
@@ -398,6 +515,7 @@ extern "C" tr_status tr_scene_build(const tr_scene_desc *d, void *hip_stream, tr
   }
   auto bail = [&](tr_status stt) {
     std::string msg = g_err;
+    (void)hipDeviceSynchronize();  // whatever was enqueued is done with the arrays
     free_scene_arrays(s);
     delete s;
     g_err = msg;
@@ -425,85 +543,67 @@ extern "C" tr_status tr_scene_build(const tr_scene_desc *d, void *hip_stream, tr
   ALLOC(s->bounds, 6);
   ALLOC(s->total64, 2);
 #undef ALLOC
-  if (e == hipSuccess) e = hipHostMalloc((void **)&s->h_bounds, 6 * sizeof(double), hipHostMallocDefault);
-  if (e == hipSuccess) e = hipHostMalloc((void **)&s->h_total, 2 * sizeof(*s->h_total), hipHostMallocDefault);
+  if (e == hipSuccess) e = host_alloc((void **)&s->h_bounds);
+  if (e == hipSuccess) s->h_total = (unsigned long long *)(s->h_bounds + 6);
   if (e != hipSuccess)
     return bail(fail(e == hipErrorOutOfMemory ? TR_ENOMEM : TR_EDEVICE, "scene allocation: %s",
                      hipGetErrorString(e)));
   s->bytes_arrays = (size_t)s->n_s * (32 + 16) + (size_t)s->n_c * (3 * 32 + 3 * 16) +
                     (size_t)s->n_t * (3 * 32 + 3 * 16) + (size_t)N * 16;
-  // upload the caller's arrays (temporary device copies), then pack
-  double *t_sc = nullptr, *t_sr = nullptr, *t_ca = nullptr, *t_cb = nullptr, *t_cr = nullptr;
-  float *t_srgb = nullptr, *t_crgb = nullptr, *t_sop = nullptr, *t_cop = nullptr;
-  double *t_tv0 = nullptr, *t_tv1 = nullptr, *t_tv2 = nullptr;
-  float *t_trgb = nullptr, *t_top = nullptr;
-  auto free_tmp = [&]() {
-    void *p[] = {t_sc, t_sr, t_ca, t_cb, t_cr, t_srgb, t_crgb, t_sop, t_cop,
-                 t_tv0, t_tv1, t_tv2, t_trgb, t_top};
-    for (void *q : p)
-      if (q) (void)hipFree(q);
-  };
+  // upload the caller's arrays to one temporary block, then pack
   if (N > 0) {
-    e = hipSuccess;
-    if (s->n_s > 0) {
-      if (e == hipSuccess) e = dmalloc(&t_sc, 3 * s->n_s);
-      if (e == hipSuccess) e = dmalloc(&t_sr, s->n_s);
-      if (e == hipSuccess) e = dmalloc(&t_srgb, 3 * s->n_s);
-      if (e == hipSuccess) e = hipMemcpyAsync(t_sc, d->sph_center, 24 * s->n_s, hipMemcpyHostToDevice, st);
-      if (e == hipSuccess) e = hipMemcpyAsync(t_sr, d->sph_radius, 8 * s->n_s, hipMemcpyHostToDevice, st);
-      if (e == hipSuccess) e = hipMemcpyAsync(t_srgb, d->sph_rgb, 12 * s->n_s, hipMemcpyHostToDevice, st);
-      if (d->sph_opacity) {
-        if (e == hipSuccess) e = dmalloc(&t_sop, s->n_s);
-        if (e == hipSuccess) e = hipMemcpyAsync(t_sop, d->sph_opacity, 4 * s->n_s, hipMemcpyHostToDevice, st);
-      }
-    }
-    if (s->n_c > 0) {
-      if (e == hipSuccess) e = dmalloc(&t_ca, 3 * s->n_c);
-      if (e == hipSuccess) e = dmalloc(&t_cb, 3 * s->n_c);
-      if (e == hipSuccess) e = dmalloc(&t_cr, s->n_c);
-      if (e == hipSuccess) e = dmalloc(&t_crgb, 3 * s->n_c);
-      if (e == hipSuccess) e = hipMemcpyAsync(t_ca, d->cyl_a, 24 * s->n_c, hipMemcpyHostToDevice, st);
-      if (e == hipSuccess) e = hipMemcpyAsync(t_cb, d->cyl_b, 24 * s->n_c, hipMemcpyHostToDevice, st);
-      if (e == hipSuccess) e = hipMemcpyAsync(t_cr, d->cyl_radius, 8 * s->n_c, hipMemcpyHostToDevice, st);
-      if (e == hipSuccess) e = hipMemcpyAsync(t_crgb, d->cyl_rgb, 12 * s->n_c, hipMemcpyHostToDevice, st);
-      if (d->cyl_opacity) {
-        if (e == hipSuccess) e = dmalloc(&t_cop, s->n_c);
-        if (e == hipSuccess) e = hipMemcpyAsync(t_cop, d->cyl_opacity, 4 * s->n_c, hipMemcpyHostToDevice, st);
-      }
-    }
-    if (s->n_t > 0) {
-      const int64_t nt = s->n_t;
-      if (e == hipSuccess) e = dmalloc(&t_tv0, 3 * nt);
-      if (e == hipSuccess) e = dmalloc(&t_tv1, 3 * nt);
-      if (e == hipSuccess) e = dmalloc(&t_tv2, 3 * nt);
-      if (e == hipSuccess) e = dmalloc(&t_trgb, 3 * nt);
-      if (e == hipSuccess) e = hipMemcpyAsync(t_tv0, d->tri_v0, 24 * nt, hipMemcpyHostToDevice, st);
-      if (e == hipSuccess) e = hipMemcpyAsync(t_tv1, d->tri_v1, 24 * nt, hipMemcpyHostToDevice, st);
-      if (e == hipSuccess) e = hipMemcpyAsync(t_tv2, d->tri_v2, 24 * nt, hipMemcpyHostToDevice, st);
-      if (e == hipSuccess) e = hipMemcpyAsync(t_trgb, d->tri_rgb, 12 * nt, hipMemcpyHostToDevice, st);
-      if (d->tri_opacity) {
-        if (e == hipSuccess) e = dmalloc(&t_top, nt);
-        if (e == hipSuccess) e = hipMemcpyAsync(t_top, d->tri_opacity, 4 * nt, hipMemcpyHostToDevice, st);
-      }
-    }
     trh::PackArgs pk{};
     pk.n_s = s->n_s;
     pk.n_c = s->n_c;
     pk.n_t = s->n_t;
-    pk.sc = t_sc;
-    pk.sr = t_sr;
-    pk.ca = t_ca;
-    pk.cb = t_cb;
-    pk.cr = t_cr;
-    pk.tv0 = t_tv0;
-    pk.tv1 = t_tv1;
-    pk.tv2 = t_tv2;
-    pk.srgb = t_srgb;
-    pk.sop = t_sop;
-    pk.crgb = t_crgb;
-    pk.cop = t_cop;
-    pk.trgb = t_trgb;
-    pk.top = t_top;
+    struct Part {
+      const void *src;
+      size_t bytes, at;
+      const void **dst;
+    };
+    std::vector<Part> parts;
+    size_t total = 0;
+    const auto part = [&](const void *src, int64_t bytes, const void **dst) {
+      if (!src || bytes == 0) return;
+      parts.push_back(Part{src, (size_t)bytes, total, dst});
+      total += ((size_t)bytes + 255) & ~(size_t)255;
+    };
+    part(d->sph_center, 24 * s->n_s, (const void **)&pk.sc);
+    part(d->sph_radius, 8 * s->n_s, (const void **)&pk.sr);
+    part(d->sph_rgb, 12 * s->n_s, (const void **)&pk.srgb);
+    part(d->sph_opacity, 4 * s->n_s, (const void **)&pk.sop);
+    part(d->cyl_a, 24 * s->n_c, (const void **)&pk.ca);
+    part(d->cyl_b, 24 * s->n_c, (const void **)&pk.cb);
+    part(d->cyl_radius, 8 * s->n_c, (const void **)&pk.cr);
+    part(d->cyl_rgb, 12 * s->n_c, (const void **)&pk.crgb);
+    part(d->cyl_opacity, 4 * s->n_c, (const void **)&pk.cop);
+    part(d->tri_v0, 24 * s->n_t, (const void **)&pk.tv0);
+    part(d->tri_v1, 24 * s->n_t, (const void **)&pk.tv1);
+    part(d->tri_v2, 24 * s->n_t, (const void **)&pk.tv2);
+    part(d->tri_rgb, 12 * s->n_t, (const void **)&pk.trgb);
+    part(d->tri_opacity, 4 * s->n_t, (const void **)&pk.top);
+    char *tmp = nullptr;
+    e = dev_alloc((void **)&tmp, total);
+    std::unique_lock<std::mutex> stage(g_stage_mu, std::defer_lock);
+    if (e == hipSuccess && total <= kStageBytes && stage.try_lock() && g_stage_cap < total) {
+      if (g_stage) (void)hipHostFree(g_stage);
+      g_stage = nullptr;
+      g_stage_cap = 0;
+      const size_t cap = std::min(kStageBytes, block_size(2 * total));
+      if (hipHostMalloc((void **)&g_stage, cap, hipHostMallocPortable) == hipSuccess) {
+        g_stage_cap = cap;
+      } else {  // (then array by array)
+        (void)hipGetLastError();
+        g_stage = nullptr;
+      }
+    }
+    const bool staged = stage.owns_lock() && g_stage_cap >= total;
+    for (const Part &q : parts) {
+      *q.dst = tmp + q.at;
+      if (staged) std::memcpy(g_stage + q.at, q.src, q.bytes);
+      else if (e == hipSuccess) e = hipMemcpyAsync(tmp + q.at, q.src, q.bytes, hipMemcpyHostToDevice, st);
+    }
+    if (staged && e == hipSuccess) e = hipMemcpyAsync(tmp, g_stage, total, hipMemcpyHostToDevice, st);
     pk.sph64 = s->sph64;
     pk.cylA64 = s->cylA64;
     pk.cylW64 = s->cylW64;
@@ -513,8 +613,9 @@ extern "C" tr_status tr_scene_build(const tr_scene_desc *d, void *hip_stream, tr
     pk.triC64 = s->triC64;
     pk.albedo = s->albedo;
     if (e == hipSuccess) e = trh::launch_pack(pk, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    free_tmp();
+    const hipError_t es = hipStreamSynchronize(st);  // (also on an error: copies may be under way)
+    if (e == hipSuccess) e = es;
+    dev_free(tmp);
     if (e != hipSuccess)
       return bail(fail(e == hipErrorOutOfMemory ? TR_ENOMEM : TR_EDEVICE, "scene upload: %s",
                        hipGetErrorString(e)));
@@ -548,7 +649,7 @@ extern "C" tr_status tr_scene_build_bvh(tr_scene *s, void *hip_stream) {
   s->bvh_depth = 0;
   const int64_t n_nodes = n >= 2 ? n - 1 : 0;
   if (s->bvh_nodes && s->bvh_cap != n_nodes) {
-    HIP_TRY(hipFree(s->bvh_nodes));
+    dev_free(s->bvh_nodes);  // (the device was synchronised above)
     s->bvh_nodes = nullptr;
     s->bvh_cap = 0;
   }
@@ -574,7 +675,7 @@ extern "C" tr_status tr_scene_build_bvh(tr_scene *s, void *hip_stream) {
                  o_ibox = carve(48 * n_nodes),
                  o_scan = carve(4 * (size_t)trh::scan_scratch_u32(trh::bvh_sort_counts(n)));
     char *base = nullptr;
-    hipError_t e = hipMalloc((void **)&base, total);
+    hipError_t e = dev_alloc((void **)&base, total);
     if (e == hipSuccess) {
       w.keys = (uint32_t *)(base + o_keys);
       w.vals = (uint32_t *)(base + o_vals);
@@ -612,9 +713,10 @@ extern "C" tr_status tr_scene_build_bvh(tr_scene *s, void *hip_stream) {
       e = trh::launch_bvh_boxes(a, w, max_dep, s->gp.delta, s->org, s->bvh_nodes, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     depth = max_dep + 1;  // internal nodes on the longest root-to-leaf path
-    if (base) (void)hipFree(base);
+    if (e != hipSuccess) (void)hipDeviceSynchronize();
+    dev_free(base);
     if (e != hipSuccess) {
-      (void)hipFree(s->bvh_nodes);
+      dev_free(s->bvh_nodes);
       s->bvh_nodes = nullptr;
       s->bvh_cap = 0;
       return fail(e == hipErrorOutOfMemory ? TR_ENOMEM : TR_EDEVICE, "BVH build: %s", hipGetErrorString(e));
@@ -1448,7 +1550,6 @@ struct NoAllocScratch {
   uint32_t counter[trd::kQueueWords];  // tile queue counters, stall flag
 };
 static __device__ __align__(256) unsigned char scratch[sizeof(NoAllocScratch)];
-constexpr int kMaxDevices = 64;
 static NoAllocScratch *g_scratch[kMaxDevices];
 static std::mutex g_scratch_mu;
 
