@@ -106,6 +106,7 @@ __device__ __forceinline__ void write_tile(const LdsT &L, int32_t b, int32_t lan
 }
 
 constexpr int kStack = trh::kBvhStack;  // BVH traversal stack entries per lane
+constexpr int kLdsStack = 16;           // of those, in LDS; the rest, seldom reached, in scratch
 
 template <int BANKS, bool TRANS, bool BVH>
 struct Lds {
@@ -133,7 +134,7 @@ struct Lds {
   float acc_r[NT], acc_g[NT], acc_b[NT], trn[NT];
   uint8_t layer[NT];
   // BVH walk: per lane a stack of node / leaf items, entry e at e * 64 + lane
-  int32_t stk[BVH ? 64 * kStack : 1];
+  int32_t stk[BVH ? 64 * kLdsStack : 1];
   // the skip rule of the slot's secondary rays (see Ray::skip)
   __device__ __forceinline__ int32_t slot_skip(int32_t slot) const {
     const int32_t k = prim[slot];
@@ -521,9 +522,9 @@ __device__ __forceinline__ int32_t find_job(const TR_CONST JobDev *jobs, int32_t
 template <int BANKS, bool RESOLVE, bool COUNT, bool TRANS, bool TRI, bool BVH>
 // Occupancy targets: 5 waves per SIMD for the plain two-bank kernel (96
 // VGPRs); compositing adds LDS state that allows fewer waves anyway, and the
-// triangle test needs more registers than 96 without spilling; the BVH
-// walk's per-lane stacks (12 KB of LDS per wave) leave room for 2.
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? 2 : (TRANS ? 3 : (BANKS <= 2 && !COUNT && !TRI ? 5 : 4))))) void k_render_wave(const WaveArgs A) {
+// triangle test needs more registers than 96 without spilling; so does the
+// BVH walk (4 waves).
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS == 1 ? (TRI ? 4 : 5) : (TRI ? 3 : 4)) : (TRANS ? 3 : (BANKS <= 2 && !COUNT && !TRI ? 5 : 4))))) void k_render_wave(const WaveArgs A) {
   __shared__ Lds<BANKS, TRANS, BVH> L;
   constexpr int NS = BANKS * 64;
   constexpr int kMinIters = 2;
@@ -566,6 +567,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? 2 : (T
   const uint64_t c_cyc_start = COUNT ? clock64() : 0;
 
   // ---- per-lane state
+  int32_t deep[BVH ? kStack - kLdsStack : 1];  // the stack's upper part
+  const auto push = [&](int32_t sp, int32_t item) {
+    if (sp < kLdsStack) L.stk[sp * 64 + lane] = item;
+    else deep[sp - kLdsStack] = item;
+  };
+  const auto peek = [&](int32_t sp) {
+    return sp < kLdsStack ? L.stk[sp * 64 + lane] : deep[sp - kLdsStack];
+  };
   int32_t kind = kIdle;
   int32_t st = kDone;  // kRun, kDone, or kPaused (waiting for an FP64 re-solve of primitive gk)
   int32_t gk = 0;
@@ -1179,7 +1188,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? 2 : (T
           int32_t sp = R.cx;
           if (hitL && hitR) {
             if (sp < kStack) {
-              L.stk[sp * 64 + lane] = lfirst ? cr : cl;
+              push(sp, lfirst ? cr : cl);
               ++sp;
             } else if (COUNT) {
               ++l_ovf;
@@ -1189,7 +1198,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? 2 : (T
           bool have = hitL || hitR;
           if (!have && sp > 0) {
             --sp;
-            item = L.stk[sp * 64 + lane];
+            item = peek(sp);
             have = true;
           }
           R.cx = sp;
@@ -1354,7 +1363,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? 2 : (T
             const bool have = sp > 0;
             if (have) {
               --sp;
-              item = L.stk[sp * 64 + lane];
+              item = peek(sp);
             }
             R.cx = sp;
             R.rc = have && item >= 0 ? item : -1;
