@@ -668,10 +668,10 @@ extern "C" tr_status tr_scene_build_bvh(tr_scene *s, void *hip_stream) {
       return at;
     };
     const size_t o_keys = carve(4 * n), o_vals = carve(4 * n), o_keys2 = carve(4 * n),
-                 o_vals2 = carve(4 * n), o_pl = carve(4 * n),
+                 o_vals2 = carve(4 * n), o_other = carve(4 * n),
                  o_flags = carve(4 * (size_t)trh::bvh_sort_counts(n)),
                  o_left = carve(4 * n_nodes), o_right = carve(4 * n_nodes),
-                 o_pi = carve(4 * n_nodes), o_arr = carve(4 * n_nodes), o_h = carve(4 * n_nodes),
+                 o_pi = carve(4 * n_nodes), o_h = carve(4 * n_nodes),
                  o_ibox = carve(48 * n_nodes),
                  o_scan = carve(4 * (size_t)trh::scan_scratch_u32(trh::bvh_sort_counts(n)));
     char *base = nullptr;
@@ -681,12 +681,11 @@ extern "C" tr_status tr_scene_build_bvh(tr_scene *s, void *hip_stream) {
       w.vals = (uint32_t *)(base + o_vals);
       w.keys2 = (uint32_t *)(base + o_keys2);
       w.vals2 = (uint32_t *)(base + o_vals2);
-      w.parent_l = (int32_t *)(base + o_pl);
+      w.other = (int32_t *)(base + o_other);
       w.flags = (uint32_t *)(base + o_flags);
       w.left = (int32_t *)(base + o_left);
       w.right = (int32_t *)(base + o_right);
       w.parent_i = (int32_t *)(base + o_pi);
-      w.arrivals = (uint32_t *)(base + o_arr);
       w.height = (int32_t *)(base + o_h);
       w.ibox = (double *)(base + o_ibox);
       w.scan_scratch = (uint32_t *)(base + o_scan);
@@ -701,16 +700,23 @@ extern "C" tr_status tr_scene_build_bvh(tr_scene *s, void *hip_stream) {
     a.triA64 = s->triA64;
     a.triB64 = s->triB64;
     a.triC64 = s->triC64;
-    // hierarchy and node depths, then the boxes level by level (the host
-    // reads the largest depth in between), then the records
-    int32_t max_dep = -1;
+    // hierarchy and node depths, then the boxes; for a large tree level by
+    // level, so the host reads the largest depth in between
+    int32_t max_dep = 0;
+    const bool small = trh::bvh_small(n);
+    const auto read_depth = [&]() {
+      if (e == hipSuccess) e = hipStreamSynchronize(st);
+      if (e == hipSuccess) std::memcpy(&max_dep, s->h_total, sizeof(int32_t));
+      if (e == hipSuccess && (max_dep < 0 || max_dep > 63)) e = hipErrorUnknown;  // cannot happen
+    };
     if (e == hipSuccess) e = trh::launch_bvh_tree(a, s->gp.lo, s->gp.hi, w, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(s->h_total, w.flags, sizeof(uint32_t), hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e == hipSuccess) std::memcpy(&max_dep, s->h_total, sizeof(int32_t));
-    if (e == hipSuccess && (max_dep < 0 || max_dep > 63)) e = hipErrorUnknown;  // cannot happen
+    if (!small) {
+      if (e == hipSuccess) e = hipMemcpyAsync(s->h_total, w.flags, sizeof(uint32_t), hipMemcpyDeviceToHost, st);
+      read_depth();
+    }
     if (e == hipSuccess)
-      e = trh::launch_bvh_boxes(a, w, max_dep, s->gp.delta, s->org, s->bvh_nodes, st);
+      e = trh::launch_bvh_boxes(a, w, max_dep, s->gp.delta, s->org, s->bvh_nodes, s->h_total, st);
+    if (small) read_depth();
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     depth = max_dep + 1;  // internal nodes on the longest root-to-leaf path
     if (e != hipSuccess) (void)hipDeviceSynchronize();

@@ -77,17 +77,18 @@ int64_t scan_scratch_u32(int64_t n);
 hipError_t launch_scan(uint32_t *data, int64_t n_plus_1, uint32_t *scratch, hipStream_t st);
 
 // Linear BVH over all primitives (n >= 2): 4 float4 per internal node (see
-// k_bvh_pack); node 0 is the root.  Scratch sizes: keys, vals, keys2, vals2,
-// parent_l: n; flags (the sort's digit counts): bvh_sort_counts(n); left,
-// right, parent_i, arrivals, height: n - 1; ibox: 6 (n - 1) doubles;
-// scan_scratch: scan_scratch_u32(bvh_sort_counts(n)).
+// k_bvh_pack); node 0 is the root.  Scratch sizes: keys, vals, keys2, vals2: n;
+// flags (the sort's digit counts): bvh_sort_counts(n); left, right, parent_i,
+// other, height: n - 1; ibox: 6 (n - 1) doubles; scan_scratch:
+// scan_scratch_u32(bvh_sort_counts(n)).
 // launch_bvh_tree sorts, builds the hierarchy and leaves each internal
 // node's depth (links from the root) in height[] and the largest depth in
-// flags[0]; launch_bvh_boxes then computes the boxes level by level from
-// that depth up and packs the records.
+// flags[0]; launch_bvh_boxes then computes the boxes from the deepest nodes up
+// and packs the records.  A small tree (bvh_small) needs no max_depth from the
+// host, and leaves the largest depth in *h_depth (pinned).
 struct BvhScratch {
-  uint32_t *keys, *vals, *keys2, *vals2, *flags, *scan_scratch, *arrivals;
-  int32_t *left, *right, *parent_i, *parent_l, *height;
+  uint32_t *keys, *vals, *keys2, *vals2, *flags, *scan_scratch;
+  int32_t *left, *right, *parent_i, *other, *height;
   double *ibox;
 };
 // Entries of the BVH walk's per-lane traversal stack.  A walk that visits a
@@ -98,7 +99,9 @@ int64_t bvh_sort_counts(int64_t n);
 hipError_t launch_bvh_tree(const BuildArgs &a, const double lo[3], const double hi[3],
                            BvhScratch &w, hipStream_t st);
 hipError_t launch_bvh_boxes(const BuildArgs &a, const BvhScratch &w, int32_t max_depth,
-                            double margin, const double origin[3], float4 *nodes, hipStream_t st);
+                            double margin, const double origin[3], float4 *nodes,
+                            unsigned long long *h_depth, hipStream_t st);
+bool bvh_small(int64_t n);
 
 // ---- frame output (frame_out.hip) ----
 // values -> bytes, floor(clamp(v, 0, 1) * 255 + 1/2); any alignment
