@@ -106,7 +106,7 @@ __device__ __forceinline__ void write_tile(const LdsT &L, int32_t b, int32_t lan
 }
 
 constexpr int kStack = trh::kBvhStack;  // BVH traversal stack entries per lane
-constexpr int kLdsStack = 16;           // of those, in LDS; the rest, seldom reached, in scratch
+constexpr int kLdsStack = 12;           // of those, in LDS; the rest, seldom reached, in scratch
 
 template <int BANKS, bool TRANS, bool BVH>
 struct Lds {
@@ -522,9 +522,12 @@ __device__ __forceinline__ int32_t find_job(const TR_CONST JobDev *jobs, int32_t
 template <int BANKS, bool RESOLVE, bool COUNT, bool TRANS, bool TRI, bool BVH>
 // Occupancy targets: 5 waves per SIMD for the plain two-bank kernel (96
 // VGPRs); compositing adds LDS state that allows fewer waves anyway, and the
-// triangle test needs more registers than 96 without spilling; so does the
-// BVH walk (4 waves).
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS == 1 ? (TRI ? 4 : 5) : (TRI ? 3 : 4)) : (TRANS ? 3 : (BANKS <= 2 && !COUNT && !TRI ? 5 : 4))))) void k_render_wave(const WaveArgs A) {
+// triangle test needs more registers than 96 without spilling.  The BVH walk
+// is bound by the latency of its node loads, and wants waves: one workgroup
+// per entry, 26,318 objects at 965x1137: 1862 us with 5, 1757 with 6, 2298
+// with 7, 3520 with 8 (registers spill); 26,560 triangles: 1784 with 4, 1700
+// with 5, 1893 with 6.  12 stack entries in LDS let 6 waves fit.
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS == 1 ? (TRI ? 5 : 6) : (TRI ? 3 : 4)) : (TRANS ? 3 : (BANKS <= 2 && !COUNT && !TRI ? 5 : 4))))) void k_render_wave(const WaveArgs A) {
   __shared__ Lds<BANKS, TRANS, BVH> L;
   constexpr int NS = BANKS * 64;
   constexpr int kMinIters = 2;
