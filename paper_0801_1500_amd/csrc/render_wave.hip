@@ -520,14 +520,18 @@ __device__ __forceinline__ int32_t find_job(const TR_CONST JobDev *jobs, int32_t
 
 // BANKS = 1: one workgroup per entry (group_entry), no tile queue.
 template <int BANKS, bool RESOLVE, bool COUNT, bool TRANS, bool TRI, bool BVH>
-// Occupancy targets: 5 waves per SIMD for the plain two-bank kernel (96
-// VGPRs); compositing adds LDS state that allows fewer waves anyway, and the
-// triangle test needs more registers than 96 without spilling.  The BVH walk
+// Occupancy targets.  With one workgroup per entry (BANKS = 1): 5 waves per
+// SIMD, 6 with compositing, whose cell loads are waited for more often; at the
+// next step registers spill in the loop.  965x1137 layers 2059 us with 3 waves,
+// 1842 with 5, 1786 with 6, 2661 with 7; 1930x2274 triangles 4524 with 4, 3964
+// with 5, 5696 with 6; 965x1137 spheres and cylinders 998 with 4, 900 with 5,
+// 1020 with 6.  Persistent waves hold 2 or 3 banks in LDS, and are left where
+// they measured best: 5 for plain scenes, 4 with triangles, 3 compositing.  The BVH walk
 // is bound by the latency of its node loads, and wants waves: one workgroup
 // per entry, 26,318 objects at 965x1137: 1862 us with 5, 1757 with 6, 2298
 // with 7, 3520 with 8 (registers spill); 26,560 triangles: 1784 with 4, 1700
 // with 5, 1893 with 6.  12 stack entries in LDS let 6 waves fit.
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS == 1 ? (TRI ? 5 : 6) : (TRI ? 3 : 4)) : (TRANS ? 3 : (BANKS <= 2 && !COUNT && !TRI ? 5 : 4))))) void k_render_wave(const WaveArgs A) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS == 1 ? (TRI ? 5 : 6) : (TRI ? 3 : 4)) : (BANKS == 1 ? (TRANS && !TRI ? 6 : 5) : (TRANS ? 3 : (BANKS <= 2 && !COUNT && !TRI ? 5 : 4)))))) void k_render_wave(const WaveArgs A) {
   __shared__ Lds<BANKS, TRANS, BVH> L;
   constexpr int NS = BANKS * 64;
   constexpr int kMinIters = 2;
