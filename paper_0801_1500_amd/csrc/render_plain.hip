@@ -474,17 +474,19 @@ constexpr int kRefill64 = 32;  // lanes at work below which idle ones take new r
 
 template <bool LAYERED, bool TRI>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
-void k_render_f64(const JobDev J, int64_t n_tiles, uint32_t whole, int32_t part_log2) {
+void k_render_f64(const JobDev J, int64_t n_tiles, uint32_t whole, int32_t part_log2, int32_t chunk_log2) {
   __shared__ LdsF64 L;
   const SceneDev &S = J.sc;
   const int32_t lane = threadIdx.x;
-  const int64_t entry = group_entry(blockIdx.x, whole, part_log2, n_tiles);
+  const int64_t entry = group_entry(blockIdx.x, whole, part_log2, chunk_log2, n_tiles);
   if (entry < 0) return;
   const uint32_t tile = (uint32_t)(entry >> 7), tiles_x = ((uint32_t)J.W + 7u) / 8u;
+  int32_t tx = (int32_t)(tile % tiles_x), ty = (int32_t)(tile / tiles_x);
+  if (chunk_log2) block_tile(tile, tiles_x, ((uint32_t)J.H + 7u) / 8u, chunk_log2, tx, ty);
   const int32_t part = (int32_t)(entry & 127) - 1;
   const int32_t npx = part < 0 ? 64 : 64 >> part_log2;
   const int32_t px = lane + (part < 0 ? 0 : part * npx);  // pixel of the tile
-  const int32_t i = (int32_t)(tile % tiles_x) * 8 + (px & 7), j = (int32_t)(tile / tiles_x) * 8 + (px >> 3);
+  const int32_t i = tx * 8 + (px & 7), j = ty * 8 + (px >> 3);
   const bool mine = lane < npx && i < J.W && j < J.H;
   const int64_t pid = (int64_t)j * J.W + i;
 
@@ -580,8 +582,7 @@ void k_render_f64(const JobDev J, int64_t n_tiles, uint32_t whole, int32_t part_
           for (int q = 0; q < 3; ++q) w.o[q] = L.P[q][slot];
           if (ao) {
             const int32_t sp = slot + (part < 0 ? 0 : part * npx);
-            const uint32_t spid = (uint32_t)(((int64_t)((int32_t)(tile / tiles_x) * 8 + (sp >> 3))) * J.W +
-                                             (int32_t)(tile % tiles_x) * 8 + (sp & 7));
+            const uint32_t spid = (uint32_t)((int64_t)(ty * 8 + (sp >> 3)) * J.W + tx * 8 + (sp & 7));
             const double N[3] = {L.N[0][slot], L.N[1][slot], L.N[2][slot]};
             uint32_t b1, b2;
             ao_uniform_bits(spid, (r - (uint32_t)J.n_lights) + ((uint32_t)layer << 16), J.view_id,
@@ -675,12 +676,12 @@ hipError_t launch_render_plain_f64(const trd::JobDev &job, uint64_t *stats, hipS
     return hipGetLastError();
   }
   const int64_t tiles = (int64_t)((job.W + 7) / 8) * ((job.H + 7) / 8);
-  const Groups g = split_groups(tiles, 1);
+  const Groups g = split_groups(tiles, 1, true, true);
   const unsigned n = (unsigned)g.workgroups;
-  if (lay && tri) k_render_f64<true, true><<<n, 64, 0, st>>>(job, tiles, g.whole, g.part_log2);
-  else if (lay) k_render_f64<true, false><<<n, 64, 0, st>>>(job, tiles, g.whole, g.part_log2);
-  else if (tri) k_render_f64<false, true><<<n, 64, 0, st>>>(job, tiles, g.whole, g.part_log2);
-  else k_render_f64<false, false><<<n, 64, 0, st>>>(job, tiles, g.whole, g.part_log2);
+  if (lay && tri) k_render_f64<true, true><<<n, 64, 0, st>>>(job, tiles, g.whole, g.part_log2, g.chunk_log2);
+  else if (lay) k_render_f64<true, false><<<n, 64, 0, st>>>(job, tiles, g.whole, g.part_log2, g.chunk_log2);
+  else if (tri) k_render_f64<false, true><<<n, 64, 0, st>>>(job, tiles, g.whole, g.part_log2, g.chunk_log2);
+  else k_render_f64<false, false><<<n, 64, 0, st>>>(job, tiles, g.whole, g.part_log2, g.chunk_log2);
   return hipGetLastError();
 }
 

@@ -506,6 +506,7 @@ struct WaveArgs {
   // launches of one workgroup per entry (BANKS = 1):
   uint32_t whole;       // groups of 8 tiles that are entries as they are; the later tiles are split
   int32_t part_log2;    // entries of a split tile, log2
+  int32_t chunk_log2;   // tiles dealt together to an XCD, log2: blocks of whole frames, or 0
 };
 
 __device__ __forceinline__ int32_t find_job(const TR_CONST JobDev *jobs, int32_t n, int64_t tile) {
@@ -553,7 +554,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS
   int32_t cur_key = -1;   // scene loaded in this wave
   int32_t scene_job = 0;  // a job whose scene is the current one
   if (SPLIT) {
-    held_tile = group_entry(blockIdx.x, A.whole, A.part_log2, A.n_tiles);
+    held_tile = group_entry(blockIdx.x, A.whole, A.part_log2, A.chunk_log2, A.n_tiles);
     if (held_tile < 0) return;
     held_job = scene_job = uni(find_job((const TR_CONST JobDev *)A.jobs, A.n_jobs, held_tile >> 7));
   }
@@ -935,7 +936,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS
           const uint32_t tl =
               (uint32_t)((SPLIT ? held_tile >> 7 : held_tile) - J->queue_begin + J->tile_begin);
           const uint32_t txs = (uint32_t)J->tiles_x;
-          const int32_t ty = (int32_t)(tl / txs), tx = (int32_t)(tl - (uint32_t)ty * txs);
+          int32_t ty, tx;
+          if (SPLIT && A.chunk_log2) {  // (then tl counts a whole frame's tiles)
+            block_tile(tl, txs, (uint32_t)J->tiles_y, A.chunk_log2, tx, ty);
+          } else {
+            ty = (int32_t)(tl / txs);
+            tx = (int32_t)(tl - (uint32_t)ty * txs);
+          }
           int32_t x0 = tx * TW, y0 = ty * TH, pw = TW, ph = TH;
           if (SPLIT && (held_tile & 127)) {  // a part: 64 >> part_log2 pixels, row-major
             const int32_t twl = __builtin_ctz((uint32_t)TW), pl = 6 - A.part_log2;
@@ -1580,6 +1587,7 @@ static hipError_t launch_t(const WaveLaunch &L, hipStream_t st) {
   a.stripe_log2 = __builtin_ctz((unsigned)L.stripe);
   a.whole = L.whole;
   a.part_log2 = L.part_log2;
+  a.chunk_log2 = L.chunk_log2;
   k_render_wave<BANKS, RES, CNT, TRANS, TRI, BVH><<<L.n_waves, 64, 0, st>>>(a);
   return hipGetLastError();
 }

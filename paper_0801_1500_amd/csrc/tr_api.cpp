@@ -1366,18 +1366,25 @@ static int64_t set_queue(JobDev *jobs, int32_t n) {
 // waves per compute unit or the stripe, and launches with a stats buffer,
 // whose counters every wave adds to at its end (about 7 ns an atomic on one
 // line: 35 ns for each of tens of thousands of workgroups).
-static void set_entries(trh::WaveLaunch &L, int64_t total, const tr_tune &t) {
+static void set_entries(trh::WaveLaunch &L, const JobDev *jobs, int64_t total, const tr_tune &t) {
   tr_tune d;
   default_tune(&d);
   L.part_log2 = -1;
   L.whole = 0;
+  L.chunk_log2 = 0;
   L.n_waves = (int32_t)std::min((int64_t)num_cus() * t.waves_per_cu, total);
   if (t.banks != d.banks || t.waves_per_cu != d.waves_per_cu || t.stripe != d.stripe ||
       L.stats || total > ((int64_t)1 << 27))
     return;
-  const trh::Groups g = trh::split_groups(total, L.n_jobs);
+  bool whole_frames = true, one_scene = true;
+  for (int32_t i = 0; i < L.n_jobs; ++i) {
+    whole_frames &= jobs[i].tile_begin == 0 && jobs[i].tile_end == (int64_t)jobs[i].tiles_x * jobs[i].tiles_y;
+    one_scene &= jobs[i].scene_key == jobs[0].scene_key;
+  }
+  const trh::Groups g = trh::split_groups(total, L.n_jobs, whole_frames, one_scene);
   L.whole = g.whole;
   L.part_log2 = g.part_log2;
+  L.chunk_log2 = g.chunk_log2;
   L.n_waves = (int32_t)g.workgroups;
 }
 
@@ -1396,7 +1403,7 @@ static trh::WaveLaunch wave_launch(const JobDev *jobs, int32_t n, int64_t total,
   L.refill_below = t.refill_below;
   L.count_ops = t.count_ops;
   L.stripe = t.stripe;
-  set_entries(L, total, t);
+  set_entries(L, jobs, total, t);
   L.resolve = jobs[0].resolve;
   L.trans = 0;
   L.tri = 0;

@@ -63,19 +63,33 @@ constexpr int kQueueWords = (kQueueXcds + 1) * kQueueStride;
 // Entry of workgroup b in a launch of one workgroup per entry: 128 tile + (0
 // for a whole tile, part + 1 for one of 2^part_log2 equal parts of its
 // row-major pixels), or -1 past the launch's tiles.  Group j of 8 consecutive
-// tiles goes to the 8 XCDs, one tile each (workgroup b runs on XCD b mod 8),
-// rotated by a hash of j: without the rotation a frame of 8 k tiles a row
-// gives each XCD the same columns in every row, and the XCDs of the middle
-// columns finish last.
+// chunks of 2^chunk_log2 tiles goes to the 8 XCDs, one chunk each (workgroup b
+// runs on XCD b mod 8), rotated: without the rotation a frame of 8 k chunks a
+// row gives each XCD the same columns in every row, and the XCDs of the middle
+// columns finish last.  Chunks are rotated by j, single tiles by a hash of j.
 __device__ __forceinline__ int64_t group_entry(uint32_t b, uint32_t whole, int32_t part_log2,
-                                               int64_t n_tiles) {
+                                               int32_t chunk_log2, int64_t n_tiles) {
   const uint32_t e = b / kQueueXcds;
   const uint32_t split = e < whole ? 0u : e - whole;
-  const uint32_t j = e < whole ? e : whole + (split >> part_log2);
-  const uint32_t q = (b + ((j * 0x9E3779B1u) >> 29)) % kQueueXcds;
-  const int64_t tile = (int64_t)j * kQueueXcds + q;
+  const uint32_t i = e < whole ? e : whole + (split >> part_log2);
+  const uint32_t j = i >> chunk_log2;
+  const uint32_t q = (b + (chunk_log2 ? j : (j * 0x9E3779B1u) >> 29)) % kQueueXcds;
+  const int64_t tile =
+      (((int64_t)j * kQueueXcds + q) << chunk_log2) + (int64_t)(i & ((1u << chunk_log2) - 1u));
   const uint32_t part = e < whole ? 0u : (split & ((1u << part_log2) - 1u)) + 1u;
   return tile < n_tiles ? (tile << 7) | part : -1;
+}
+
+// Tile t of a whole frame launched in chunks: bands of rows, each dealt column
+// by column, so that a chunk is a block of tiles (8 x 4 of 32, 16 x 8 of 128;
+// the last band has the rows that are left).
+__device__ __forceinline__ void block_tile(uint32_t t, uint32_t tiles_x, uint32_t tiles_y,
+                                           int32_t chunk_log2, int32_t &tx, int32_t &ty) {
+  const uint32_t band = 1u << ((chunk_log2 + 1) >> 1);
+  const uint32_t k = t / (band * tiles_x), r = t - k * band * tiles_x;
+  const uint32_t rows = min(band, tiles_y - k * band);
+  tx = (int32_t)(r / rows);
+  ty = (int32_t)(k * band + r - (uint32_t)tx * rows);
 }
 
 // ----------------------------------------------------------------- scene
