@@ -160,7 +160,6 @@ __device__ __forceinline__ void pack32(const trh::BuildArgs &a, const trh::Pack3
   const int64_t n_s = a.n_s, n_c = a.n_c;
   const double4 *sph64 = a.sph64, *cylA64 = a.cylA64, *cylB64 = a.cylB64, *cylW64 = P.cylW64;
   float4 *sph32 = P.sph32, *cylA32 = P.cylA32, *cylW32 = P.cylW32;
-  float4 *triV32 = P.triV32, *triE1_32 = P.triE1_32, *triE2_32 = P.triE2_32;
   const double ox = P.origin[0], oy = P.origin[1], oz = P.origin[2];
   double ext = 0.0;  // this primitive's farthest point from the centre
   if (k >= n_s + n_c && k < n_s + n_c + a.n_t) {
@@ -173,12 +172,12 @@ __device__ __forceinline__ void pack32(const trh::BuildArgs &a, const trh::Pack3
     const double nx = e1[1] * e2[2] - e1[2] * e2[1];
     const double ny = e1[2] * e2[0] - e1[0] * e2[2];
     const double nz = e1[0] * e2[1] - e1[1] * e2[0];
-    triV32[m] = make_float4((float)(A.x - ox), (float)(A.y - oy), (float)(A.z - oz),
-                            (float)sqrt((nx * nx + ny * ny) + nz * nz));
+    P.tri32[3 * m] = make_float4((float)(A.x - ox), (float)(A.y - oy), (float)(A.z - oz),
+                                 (float)sqrt((nx * nx + ny * ny) + nz * nz));
     ext = fmax(dist3(A.x - ox, A.y - oy, A.z - oz),
                fmax(dist3(B.x - ox, B.y - oy, B.z - oz), dist3(C.x - ox, C.y - oy, C.z - oz)));
-    triE1_32[m] = make_float4((float)e1[0], (float)e1[1], (float)e1[2], 0.0f);
-    triE2_32[m] = make_float4((float)e2[0], (float)e2[1], (float)e2[2], 0.0f);
+    P.tri32[3 * m + 1] = make_float4((float)e1[0], (float)e1[1], (float)e1[2], 0.0f);
+    P.tri32[3 * m + 2] = make_float4((float)e2[0], (float)e2[1], (float)e2[2], 0.0f);
   }
   if (k < n_s) {
     const double4 s = sph64[k];

@@ -47,7 +47,7 @@ constexpr double kEpsD = 1e-4;
 // (nearest hit, from the hit point); kinds >= kShadow are any-hit rays.
 enum : int32_t { kIdle = 0, kPrimary = 1, kCont = 2, kShadow = 3, kAO = 4 };
 // lane state of the ray it holds (an idle lane counts as finished)
-enum : int32_t { kRun = 0, kDone = 1, kPaused = 2 };
+enum : int32_t { kRun = 0, kDone = 1, kPaused = 2 };  // (>= 0: paused)
 
 // Per-bank copy of the job fields secondary rays and shading need.
 struct BankInfo {
@@ -224,7 +224,7 @@ struct SceneHot {
   const TR_GLOBAL uint32_t *refs;
   const TR_GLOBAL trd::CellInfo *cellinfo;
   const TR_GLOBAL vf4 *sph32, *cylA32, *cylW32, *albedo;
-  const TR_GLOBAL vf4 *triV32, *triE1_32, *triE2_32;
+  const TR_GLOBAL vf4 *tri32;
   const TR_GLOBAL vf4 *bvh;  // 4 records per internal node
   int32_t bvh_n;             // primitives in the BVH
   // Inside this kernel a primitive is named by its record offset, 16 x its
@@ -242,6 +242,14 @@ struct SceneHot {
 // The job table is read-only for the whole launch, so it is read through the
 // constant address space: with a wave-uniform job index the fields are scalar
 // loads and stay in SGPRs.
+// The three records of the triangle at record offset off (16 times its index):
+// 48 bytes side by side, one or two cache lines where three arrays were three
+// (BVH walk of 26,560 triangles at 965x1137 1709 -> 1675 us; the grid walk, whose
+// cells' triangles are read over and over, the same within 1%).  (64 bits: 48
+// times an index can pass 32.)
+__device__ __forceinline__ const TR_GLOBAL vf4 *tri_record(const TR_GLOBAL vf4 *base, uint32_t off) {
+  return (const TR_GLOBAL vf4 *)((const TR_GLOBAL char *)base + (uint64_t)off * 3u);
+}
 __device__ __forceinline__ SceneHot load_hot(const JobDev *Jg) {
   const TR_CONST JobDev *J = (const TR_CONST JobDev *)Jg;
   SceneHot H;
@@ -251,9 +259,7 @@ __device__ __forceinline__ SceneHot load_hot(const JobDev *Jg) {
   H.cylA32 = (const TR_GLOBAL vf4 *)J->sc.cylA32;
   H.cylW32 = (const TR_GLOBAL vf4 *)J->sc.cylW32;
   H.albedo = (const TR_GLOBAL vf4 *)J->sc.albedo;
-  H.triV32 = (const TR_GLOBAL vf4 *)J->sc.triV32;
-  H.triE1_32 = (const TR_GLOBAL vf4 *)J->sc.triE1_32;
-  H.triE2_32 = (const TR_GLOBAL vf4 *)J->sc.triE2_32;
+  H.tri32 = (const TR_GLOBAL vf4 *)J->sc.tri32;
   H.bvh = (const TR_GLOBAL vf4 *)J->sc.bvh;
   H.bvh_n = J->sc.bvh_n;
   H.s_end = J->sc.n_s << kRecShift;
@@ -584,8 +590,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS
     return sp < kLdsStack ? L.stk[sp * 64 + lane] : deep[sp - kLdsStack];
   };
   int32_t kind = kIdle;
-  int32_t st = kDone;  // kRun, kDone, or kPaused (waiting for an FP64 re-solve of primitive gk)
   int32_t gk = 0;
+  int32_t st = kDone;  // kRun, kDone, or the primitive whose FP64 re-solve the lane waits for
   int32_t slot = 0, ridx = 0;
   Ray R;
   R.bk = -1;
@@ -661,8 +667,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS
           Ny = Py - s.y;
           Nz = Pz - s.z;
         } else if (TRI && k >= S.c_end) {  // triangle: e1 x e2
-          const vf4 e1 = ldgb(S.triE1_32, (uint32_t)(k - S.c_end));
-          const vf4 e2 = ldgb(S.triE2_32, (uint32_t)(k - S.c_end));
+          const TR_GLOBAL vf4 *T = tri_record(S.tri32, (uint32_t)(k - S.c_end));
+          const vf4 e1 = T[1], e2 = T[2];
           Nx = e1.y * e2.z - e1.z * e2.y;
           Ny = e1.z * e2.x - e1.x * e2.z;
           Nz = e1.x * e2.y - e1.y * e2.x;
@@ -1263,8 +1269,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS
           // plane (|det| against |e1 x e2|), or a hit point within 2^-12 of an
           // edge in barycentric terms.
           tested = true;
-          const uint32_t m = (uint32_t)(nkr - H.c_end);  // byte offset of its records
-          const vf4 V = ldgb(H.triV32, m), E1 = ldgb(H.triE1_32, m), E2 = ldgb(H.triE2_32, m);
+          const TR_GLOBAL vf4 *T3 = tri_record(H.tri32, (uint32_t)(nkr - H.c_end));
+          const vf4 V = T3[0], E1 = T3[1], E2 = T3[2];
           const float Px = R.dy * E2.z - R.dz * E2.y, Py = R.dz * E2.x - R.dx * E2.z,
                       Pz = R.dx * E2.y - R.dy * E2.x;
           const float det = E1.x * Px + E1.y * Py + E1.z * Pz;

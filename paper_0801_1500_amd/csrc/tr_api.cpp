@@ -180,7 +180,7 @@ struct tr_scene {
   int64_t bvh_n = 0;            // primitives it covers (0 = not built)
   int64_t bvh_cap = 0;          // internal-node records the buffer holds
   int32_t bvh_depth = 0;        // internal nodes on its longest root-to-leaf path
-  float4 *triV32 = nullptr, *triE1_32 = nullptr, *triE2_32 = nullptr;
+  float4 *tri32 = nullptr;
   uint32_t *cell_begin = nullptr, *refs = nullptr, *count = nullptr, *scan_scratch = nullptr;
   uint32_t *wrefs = nullptr;  // FP32 walk lists: per occupied cell its references, then -1
   trd::CellInfo *cellinfo = nullptr;
@@ -210,7 +210,7 @@ static void free_scene_arrays(tr_scene *s) {
   void *ptrs[] = {s->sph64, s->cylA64, s->cylW64, s->cylB64, s->sph32,       s->cylA32,
                   s->cylW32, s->albedo, s->cell_begin, s->refs, s->count, s->scan_scratch,
                   s->bounds_scratch, s->bounds, s->cellinfo, s->dist0, s->dist1, s->wrefs,
-                  s->triA64, s->triB64, s->triC64, s->triV32, s->triE1_32, s->triE2_32,
+                  s->triA64, s->triB64, s->triC64, s->tri32,
                   s->bvh_nodes, s->total64};
   for (void *p : ptrs) dev_free(p);
   if (s->counted) (void)hipEventDestroy(s->counted);
@@ -264,9 +264,7 @@ static void fill_scene_dev(tr_scene *s) {
   d.triA64 = s->triA64;
   d.triB64 = s->triB64;
   d.triC64 = s->triC64;
-  d.triV32 = s->triV32;
-  d.triE1_32 = s->triE1_32;
-  d.triE2_32 = s->triE2_32;
+  d.tri32 = s->tri32;
   d.bvh = s->bvh_nodes;
   d.bvh_n = (int32_t)s->bvh_n;
   d.bvh_depth = s->bvh_depth;
@@ -375,9 +373,7 @@ static tr_status build_grid_impl(tr_scene *s, hipStream_t st) {
   p32.sph32 = s->sph32;
   p32.cylA32 = s->cylA32;
   p32.cylW32 = s->cylW32;
-  p32.triV32 = s->triV32;
-  p32.triE1_32 = s->triE1_32;
-  p32.triE2_32 = s->triE2_32;
+  p32.tri32 = s->tri32;
   p32.rmax64 = s->total64 + 1;
   if (!s->counted) HIP_TRY(hipEventCreateWithFlags(&s->counted, hipEventDisableTiming));
   HIP_TRY(trh::launch_count_pack(a, p32, s->count, nc, s->total64, st));
@@ -536,9 +532,7 @@ extern "C" tr_status tr_scene_build(const tr_scene_desc *d, void *hip_stream, tr
   ALLOC(s->triA64, s->n_t);
   ALLOC(s->triB64, s->n_t);
   ALLOC(s->triC64, s->n_t);
-  ALLOC(s->triV32, s->n_t);
-  ALLOC(s->triE1_32, s->n_t);
-  ALLOC(s->triE2_32, s->n_t);
+  ALLOC(s->tri32, 3 * s->n_t);
   ALLOC(s->bounds_scratch, trh::bounds_scratch_doubles(N));
   ALLOC(s->bounds, 6);
   ALLOC(s->total64, 2);

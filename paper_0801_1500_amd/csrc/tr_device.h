@@ -12,7 +12,8 @@
 //   cylA32 float4[n_c], cylW32 float4[n_c]  (ax, ay, az, rho^2), (wx, wy, wz, L): two
 //                        16-byte loads per cylinder
 //   triA64/triB64/triC64 double4[n_t]  triangle vertices (FP64)
-//   triV32, triE1_32, triE2_32 float4[n_t]  (v0, |e1 x e2|), e1, e2: three loads per triangle
+//   tri32 float4[3 n_t]  per triangle (v0, |e1 x e2|), e1, e2: three loads, of one or
+//                        two cache lines
 //                        (FP32 positions are relative to org, the centre of the grid
 //                        box: lo32 = lo - org, hi32 = hi - org, eye32 = eye - org)
 //   albedo float4[N]     (r, g, b, opacity) by global id
@@ -98,7 +99,7 @@ struct SceneDev {
   const double4 *sph64, *cylA64, *cylW64;
   const double4 *triA64, *triB64, *triC64;  // triangle vertices (FP64)
   const float4 *sph32, *cylA32, *cylW32;
-  const float4 *triV32, *triE1_32, *triE2_32;  // (v0 - org, |e1 x e2|), (e1, 0), (e2, 0)
+  const float4 *tri32;  // per triangle (v0 - org, |e1 x e2|), (e1, 0), (e2, 0)
   const float4 *bvh;   // linear BVH records (4 float4 per internal node), or null
   int32_t bvh_n;       // primitives covered by the BVH (0 = none built)
   int32_t bvh_depth;   // internal nodes on the BVH's longest root-to-leaf path

@@ -43,7 +43,7 @@ hipError_t launch_pack(const PackArgs &p, hipStream_t st);
 struct Pack32Args {
   const double4 *cylW64;
   double origin[3];
-  float4 *sph32, *cylA32, *cylW32, *triV32, *triE1_32, *triE2_32;
+  float4 *sph32, *cylA32, *cylW32, *tri32;
   unsigned long long *rmax64;
 };
 // bounds: out6 = (lo xyz, hi xyz); scratch >= bounds_scratch_doubles(N) doubles
