@@ -234,9 +234,11 @@ struct SceneHot {
   int32_t s_end;  // 16 n_s
   int32_t c_end;  // 16 (n_s + n_c)
   int32_t res[3];
+  uint32_t last_cell;
   float lo32[3], hi32[3], inv32[3], h32[3];
   float org32[3];  // cell coordinate of the FP32 frame's origin
   float rb2, rguard2;  // bounding sphere (see SceneDev)
+  float exit;          // see SceneDev
 };
 
 // The job table is read-only for the whole launch, so it is read through the
@@ -273,6 +275,8 @@ __device__ __forceinline__ SceneHot load_hot(const JobDev *Jg) {
     H.h32[q] = J->sc.h32[q];
     H.org32[q] = J->sc.org32[q];
   }
+  H.last_cell = (uint32_t)(J->sc.res[0] * J->sc.res[1]) * (uint32_t)J->sc.res[2] - 1u;
+  H.exit = J->sc.exit32;
   H.rb2 = J->sc.rb2_32;
   H.rguard2 = J->sc.rguard2_32;
   return H;
@@ -367,10 +371,11 @@ __device__ __forceinline__ void shade_tile(LdsT &L, int32_t b, int32_t lane,
 }
 
 
-__device__ __forceinline__ void load_cell(Ray &R, const SceneHot &S) {
+__device__ __forceinline__ void load_cell(Ray &R, const SceneHot &S, uint32_t last = ~0u) {
   // res <= 512 per axis: the products fit the 24-bit multiplier
-  const uint32_t cell = mad24(mad24((uint32_t)R.cz, (uint32_t)S.res[1], (uint32_t)R.cy),
+  uint32_t cell = mad24(mad24((uint32_t)R.cz, (uint32_t)S.res[1], (uint32_t)R.cy),
                               (uint32_t)S.res[0], (uint32_t)R.cx);
+  if (last != ~0u) cell = min(cell, last);
   // one 8-byte load: byte offset of the cell's list in wrefs (or -distance)
   // and its first entry (-1 if empty)
   const vu2 ci = ldg((const TR_GLOBAL vu2 *)S.cellinfo, cell);
@@ -387,7 +392,9 @@ __device__ __forceinline__ bool ray_setup(Ray &R, const SceneHot &S) {
   const float ay = (S.lo32[1] - R.oy) * iy, by = (S.hi32[1] - R.oy) * iy;
   const float az = (S.lo32[2] - R.oz) * iz, bz = (S.hi32[2] - R.oz) * iz;
   float t0 = fmaxf(R.tmin, fmaxf(fmaxf(fminf(ax, bx), fminf(ay, by)), fminf(az, bz)));
-  float t1 = fminf(R.tmax, fminf(fminf(fmaxf(ax, bx), fmaxf(ay, by)), fmaxf(az, bz)));
+  // (the box's padding holds nothing: ending inside it, the walk does not
+  // enter the cells past a face whose time rounds to just before t1)
+  float t1 = fminf(R.tmax, fminf(fminf(fmaxf(ax, bx), fmaxf(ay, by)), fmaxf(az, bz)) - S.exit);
   {
     // Every hit lies inside the bounding sphere about the FP32 frame's
     // origin (the box centre), so the walk runs only over the ray's chord of
@@ -1180,7 +1187,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS
         // is issued last and consumed next iteration.
         vf4 sdat;  // (read only where is_sph; a cylinder's bounding sphere follows the spheres)
         if (is_sph) sdat = ldgb(H.sph32, (uint32_t)nkr);
-        bool enter = false;  // the step moved into a cell inside the grid
+        bool enter = false;  // the step moved on
         if (BVH && is_step) {
           // ---- BVH node: test both children's boxes against (tmin, min(t1,
           // best t)); go to the nearer hit child, stack the other; with no
@@ -1414,7 +1421,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS
           // empty block of 2M + 1 cells per axis ahead of it (0 once a cell is
           // done), and the jump takes the larger
           const int32_t mo = (int32_t)__builtin_amdgcn_ubfe((uint32_t)R.nk, (uint32_t)R.o3, 3u);
-          const int32_t nk1 = min(min(R.rc, -1), -1 - 2 * mo);
+          int32_t mo1;  // -1 - 2 mo, in one instruction
+          asm("v_mad_i32_i24 %0, %1, -2, -1" : "=v"(mo1) : "v"(mo));
+          const int32_t nk1 = min(min(R.rc, -1), mo1);
           // cell just beyond the cube on each axis; its near plane is crossed at
           // b_a + i * h_a (b_a is shifted one cell for negative steps at setup);
           // (-sign) (-k) is the offset
@@ -1442,10 +1451,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS
           R.cx = ax ? ix1 : nx;
           R.cy = ay ? iy1 : ny;
           R.cz = az ? iz1 : nz;
-          // (tn < bt is finite, so the crossed axis has a nonzero step)
-          const bool inb = ((uint32_t)R.cx < (uint32_t)H.res[0]) & ((uint32_t)R.cy < (uint32_t)H.res[1]) &
-                           ((uint32_t)R.cz < (uint32_t)H.res[2]);
-          enter = adv & inb;
+          // (tn < bt is finite, so the crossed axis has a nonzero step.)  The
+          // cell is inside the grid unless rounding took the walk past t1,
+          // which ends short of the box's faces: no test of its coordinates,
+          // only the record's index is held in range.  Such a walk ends with
+          // its next step; primitives tested there are real candidates.
+          // This and the multiply-add above, five VALU instructions of some
+          // ninety an iteration: 3860x4548 8.29 -> 8.11 ms, 8 views of 1080p
+          // of 10^6 objects 29.8 -> 29.5.
+          enter = adv;
           st = enter ? st : kDone;
           if (COUNT) {
             l_jumps += adv & (nk1 < -1);
@@ -1454,7 +1468,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS
             l_cells_sh += enter & (kind == kShadow);
           }
         }
-        if (!BVH && enter) load_cell(R, H);
+        if (!BVH && enter) load_cell(R, H, H.last_cell);
         }  // work
         work = st == kRun;
         nwork = __popcll(ballot(work));

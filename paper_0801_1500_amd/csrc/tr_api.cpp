@@ -296,6 +296,7 @@ static void fill_scene_dev(tr_scene *s) {
   }
   // the bounding sphere, padded by 2^-10 and rounded up (squares in FP64)
   const double rp = s->rbound * (1.0 + 0x1p-10);
+  d.exit32 = (float)(std::max({s->gp.hi[0] - s->gp.lo[0], s->gp.hi[1] - s->gp.lo[1], s->gp.hi[2] - s->gp.lo[2]}) / 65536.0);
   d.rb2_32 = std::nextafter((float)(rp * rp), INFINITY);
   d.rguard2_32 = (float)(rp * rp * 0x1p20);
 }

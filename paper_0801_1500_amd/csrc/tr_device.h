@@ -117,6 +117,7 @@ struct SceneDev {
   // rguard2_32 = (2^10 x the padded radius) squared, the distance from org
   // up to which a ray origin's FP32 rounding stays below the padding.
   float rb2_32, rguard2_32;
+  float exit32;  // the walk ends this far before the box's faces (under a sixth of the padding)
 };
 
 // One render job: scene + camera + parameters + outputs + its tile range.
