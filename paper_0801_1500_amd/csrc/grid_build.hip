@@ -410,25 +410,33 @@ __global__ __launch_bounds__(kBlock) void k_sort_cells(const uint32_t *cell_begi
 // separable passes g(x) = min_r max(|r|, g(x + r e_axis)): the L-infinity
 // distance is the min over occupied y of max over axes of |x_a - y_a|, and
 // max distributes over min, so the axes can be taken one at a time.
+// Bound by the latency of its byte loads where the nearest list is far: the
+// loads of kDistStep distances to both sides go out together.
 constexpr int kDistCap = 32;
+constexpr int kDistStep = 4;
 
 __global__ void k_dist_pass(const uint8_t *in, uint8_t *out, int32_t rx, int32_t ry, int32_t rz,
                             int axis, int32_t cap) {
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t n = (int64_t)rx * ry * rz;
   if (c >= n) return;
-  const int32_t ix = (int32_t)(c % rx);
-  const int32_t iy = (int32_t)((c / rx) % ry);
-  const int32_t iz = (int32_t)(c / ((int64_t)rx * ry));
+  const int32_t row = (int32_t)c / rx;  // (a grid has at most 512^3 cells)
+  const int32_t ix = (int32_t)c - row * rx, iz = row / ry, iy = row - iz * ry;
   const int32_t p = axis == 0 ? ix : (axis == 1 ? iy : iz);
   const int32_t len = axis == 0 ? rx : (axis == 1 ? ry : rz);
   const int64_t stride = axis == 0 ? 1 : (axis == 1 ? (int64_t)rx : (int64_t)rx * ry);
   int32_t best = in[c];
-  for (int32_t r = 1; r < best; ++r) {  // a neighbour r away can only give >= r
-    const int32_t a = p - r >= 0 ? (int32_t)in[c - r * stride] : cap;
-    const int32_t b = p + r < len ? (int32_t)in[c + r * stride] : cap;
-    const int32_t v = max(r, min(a, b));
-    best = min(best, v);
+  for (int32_t r0 = 1; r0 < best; r0 += kDistStep) {  // a neighbour r away can only give >= r
+    int32_t v[kDistStep];
+#pragma unroll
+    for (int32_t q = 0; q < kDistStep; ++q) {
+      const int32_t r = r0 + q;
+      const int32_t a = p - r >= 0 ? (int32_t)in[c - r * stride] : cap;
+      const int32_t b = p + r < len ? (int32_t)in[c + r * stride] : cap;
+      v[q] = max(r, min(a, b));
+    }
+#pragma unroll
+    for (int32_t q = 0; q < kDistStep; ++q) best = min(best, v[q]);
   }
   out[c] = (uint8_t)best;
 }
