@@ -1,8 +1,10 @@
-// render_wave.hip -- the FP32 persistent-wavefront ray kernel.
+// render_wave.hip -- the FP32 wavefront ray kernel.
 //
-// Each workgroup is one 64-lane wave that lives for the whole launch and
-// pulls 64-pixel tiles from a global tile counter (tiles of many frames may
-// share one launch).  A wave keeps BANKS tiles in flight.  Their pixels own
+// Each workgroup is one 64-lane wave.  By default it takes one 64-pixel tile,
+// or a part of one, and the dispatcher is the queue (BANKS = 1, group_entry);
+// launches that count, and tunings that ask for it, keep waves that live for
+// the whole launch and pull tiles from counters, BANKS tiles in flight (tiles
+// of many frames may share one launch either way).  A tile's pixels own
 // "slots" in LDS holding the shading state of a hit (point, normal, hit id,
 // pending-ray count, occlusion bits).  Primary rays, light shadow rays and
 // AO rays are all traced by the same grid-walking loop, one ray per lane:
@@ -14,7 +16,7 @@
 //            re-solved in FP64 just before this phase and resume;
 //   refill   idle lanes are compacted (ballot + mbcnt) onto the next
 //            secondary rays of the FIFO, then onto fresh primary rays, and a
-//            new tile is fetched when a bank frees;
+//            persistent wave fetches a new tile when a bank frees;
 //   traverse every busy lane advances its ray by one unit of work per
 //            iteration -- test one primitive reference, or step to the next
 //            grid cell (3D-DDA) -- until too few lanes are busy.
@@ -1549,8 +1551,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS
   }
 }
 
-__global__ void k_zero_u32(uint32_t *p) { *p = 0u; }
-
 // Job table entries written from a kernel argument (the caller's jobs need no
 // host staging buffer): one wave per job copies its 4-byte words.
 static_assert(sizeof(JobDev) % 4 == 0, "JobDev is copied as words");
@@ -1661,11 +1661,6 @@ hipError_t launch_put_jobs(const JobDev *J, int32_t n, JobDev *dst, hipStream_t 
     else if (n == 2) put_jobs<2>(J, dst, st);
     else put_jobs<1>(J, dst, st);
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_zero_counter(uint32_t *p, hipStream_t st) {
-  k_zero_u32<<<1, 1, 0, st>>>(p);
   return hipGetLastError();
 }
 

@@ -175,7 +175,6 @@ struct WaveLaunch {
   int32_t bvh;               // walk the scenes' BVHs instead of their grids
 };
 hipError_t launch_render_wave(const WaveLaunch &L, hipStream_t st);
-hipError_t launch_zero_counter(uint32_t *p, hipStream_t st);
 // write n job table entries (device memory) from the host's jobs, passed as
 // kernel arguments, kPutJobs a launch
 constexpr int kPutJobs = 3;
