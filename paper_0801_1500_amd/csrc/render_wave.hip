@@ -75,9 +75,10 @@ struct BankInfo {
 
 // Bank record of a lane's slot (bank index < BANKS): the byte offset by the
 // 24-bit multiplier (the compiler would use a slow 32-bit multiply).
-template <int BANKS>
-__device__ __forceinline__ BankInfo &bank_of(BankInfo (&bank)[BANKS], int32_t bk) {
-  return *(BankInfo *)((char *)bank + __umul24((uint32_t)bk, (uint32_t)sizeof(BankInfo)));
+template <typename LdsT>
+__device__ __forceinline__ BankInfo &bank_of(LdsT &L, int32_t bk) {
+  if (LdsT::kBank0) return L.bank[0];
+  return *(BankInfo *)((char *)L.bank + __umul24((uint32_t)bk, (uint32_t)sizeof(BankInfo)));
 }
 
 // Pixel of slot offset q (0..63) in a bank's tile: row-major over vw columns.
@@ -114,6 +115,9 @@ template <int BANKS, bool TRANS, bool BVH>
 struct Lds {
   static constexpr int NS = BANKS * 64;
   static constexpr int NT = TRANS ? NS : 1;  // transparency state only when compositing
+  // One bank: its fields at fixed addresses (3860x4548 8131 -> 8077 us; the
+  // compositing variant spills more with them, 1738 -> 1933 us, and goes without)
+  static constexpr bool kBank0 = BANKS == 1 && !TRANS;
   float px[NS], py[NS], pz[NS];
   float nx[NS], ny[NS], nz[NS];
   int32_t prim[NS];     // hit primitive (record offset)
@@ -614,12 +618,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS
     if (RESOLVE && ballot(st == kPaused)) {
       if (st == kPaused) {
         const int32_t bk = slot >> 6;
-        const JobDev *J = &A.jobs[bank_of(L.bank, bk).job];
+        const JobDev *J = &A.jobs[bank_of(L, bk).job];
         const SceneDev &S = J->sc;
         double o[3], d[3];
         if (kind == kPrimary) {
           int32_t px, py;
-          bank_pixel(bank_of(L.bank, bk), slot & 63, px, py);
+          bank_pixel(bank_of(L, bk), slot & 63, px, py);
           primary_ray_f64(*J, px, py, o, d);
         } else {  // the FP32 origin, back from the FP32 frame
           o[0] = (double)R.ox + S.org[0];
@@ -702,7 +706,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS
         }
         uint32_t lv = 0;
         bool near0 = false;  // a sign decision within 2^-12 of zero
-        const BankInfo &Bk = bank_of(L.bank, bk);
+        const BankInfo &Bk = bank_of(L, bk);
         const int32_t nl = Bk.n_lights;
         for (int l = 0; l < nl; ++l) {
           const float cl = Nx * Bk.ldir[l][0] + Ny * Bk.ldir[l][1] + Nz * Bk.ldir[l][2];
@@ -769,12 +773,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS
       if (!TRANS && finalize) {
         // shaded with the whole tile (shade_tile); a miss is marked here
         if (fin_prim_miss) L.prim[slot] = -1;
-        atomicAdd(&bank_of(L.bank, slot >> 6).done, 1);
+        atomicAdd(&bank_of(L, slot >> 6).done, 1);
       }
       if (TRANS && finalize) {
         float alpha = 1.0f;
         const int32_t bk = slot >> 6;
-        BankInfo &B = bank_of(L.bank, bk);
+        BankInfo &B = bank_of(L, bk);
         int32_t x, y;
         bank_pixel(B, slot & 63, x, y);
         const int64_t pid = (int64_t)y * B.W + x;
@@ -1037,7 +1041,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS
         const bool fresh = me_idle && kind != kIdle;
         if (fresh) {
           const SceneHot H = load_hot(&A.jobs[uni(scene_job)]);
-          const BankInfo &B = bank_of(L.bank, slot >> 6);
+          const BankInfo &B = bank_of(L, slot >> 6);
           int32_t pi, pj;
           bank_pixel(B, slot & 63, pi, pj);
           // One Philox draw serves both uses (one inlined copy keeps register
