@@ -1360,7 +1360,8 @@ static int64_t set_queue(JobDev *jobs, int32_t n) {
 // Persistent waves take what asks for them: three banks, tunings that set the
 // waves per compute unit or the stripe, and launches with a stats buffer,
 // whose counters every wave adds to at its end (about 7 ns an atomic on one
-// line: 35 ns for each of tens of thousands of workgroups).
+// line: 35 ns for each of tens of thousands of workgroups), and launches of more
+// workgroups than HIP takes (4,300 megapixels in 64 x 1 tiles).
 static void set_entries(trh::WaveLaunch &L, const JobDev *jobs, int64_t total, const tr_tune &t) {
   tr_tune d;
   default_tune(&d);
@@ -1368,15 +1369,14 @@ static void set_entries(trh::WaveLaunch &L, const JobDev *jobs, int64_t total, c
   L.whole = 0;
   L.chunk_log2 = 0;
   L.n_waves = (int32_t)std::min((int64_t)num_cus() * t.waves_per_cu, total);
-  if (t.banks != d.banks || t.waves_per_cu != d.waves_per_cu || t.stripe != d.stripe ||
-      L.stats || total > ((int64_t)1 << 27))
-    return;
+  if (t.banks != d.banks || t.waves_per_cu != d.waves_per_cu || t.stripe != d.stripe || L.stats) return;
   bool whole_frames = true, one_scene = true;
   for (int32_t i = 0; i < L.n_jobs; ++i) {
     whole_frames &= jobs[i].tile_begin == 0 && jobs[i].tile_end == (int64_t)jobs[i].tiles_x * jobs[i].tiles_y;
     one_scene &= jobs[i].scene_key == jobs[0].scene_key;
   }
   const trh::Groups g = trh::split_groups(total, L.n_jobs, whole_frames, one_scene);
+  if (g.workgroups > trh::kMaxWorkgroups) return;
   L.whole = g.whole;
   L.part_log2 = g.part_log2;
   L.chunk_log2 = g.chunk_log2;

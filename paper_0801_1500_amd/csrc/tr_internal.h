@@ -137,11 +137,14 @@ hipError_t launch_render_plain_f64(const trd::JobDev &job, uint64_t *stats, hipS
 // the L2s, 31.2, 30.2, 29.8, 29.7 ms (512 tiles: 30.8); 6 requests of mixed
 // sizes and scenes 1905, 1888, 1882, 1931.  Ranges of a frame's tiles run in
 // row order: single tiles.
+// A launch has fewer than 2^32 threads (HIP's limit for a dimension of the
+// grid); callers compare the count, split tail and all.
+constexpr int64_t kMaxWorkgroups = (int64_t)UINT32_MAX / 64;
 struct Groups {
   uint32_t whole;     // in groups of 8 tiles
   int32_t part_log2;
   int32_t chunk_log2;
-  int64_t workgroups;
+  int64_t workgroups;         // of 64 threads; may exceed kMaxWorkgroups
 };
 inline Groups split_groups(int64_t tiles, int32_t n_jobs, bool blocks, bool one_scene) {
   const int64_t split = (int64_t)((n_jobs > 1 ? 20.0 : 60.0) * std::sqrt((double)tiles));

@@ -1,0 +1,53 @@
+"""Host side of the render launches, on a model of the HIP runtime (no GPU):
+launch sizes at the runtime's limit of 2^32 work-items per dimension."""
+import ctypes as C
+
+import pytest
+
+import hip_model
+import scenegen
+
+LIMIT = 2 ** 26  # one-wave workgroups the runtime no longer launches
+
+
+def _job(tr, scene, width, height, precision="fp32_resolve", **params):
+    """One job's arguments; the frame's address is never read here."""
+    cam = scenegen.Camera((0.0, 0.0, 30.0), (0.0, 0.0, 0.0), (0.0, 1.0, 0.0), 50.0, width, height)
+    p = scenegen.Params(ao_samples=4, seed=3, **params)
+    f = tr.Frame(0x1000000, None, None, None, None)
+    return scene, tr.make_camera(cam), tr.make_params(p, precision), f
+
+
+def _render(tr, entry, jobs, stream=None):
+    n = len(jobs)
+    sc = (C.c_void_p * n)(*[j[0].handle for j in jobs])
+    cm, pr, fr = ((t * n)(*[j[k] for j in jobs]) for k, t in ((1, tr.Camera), (2, tr.Params), (3, tr.Frame)))
+    L = tr.lib()
+    if entry == "render":
+        return L.tr_render(sc[0], cm, pr, fr, stream)
+    if entry == "batch":
+        return L.tr_render_batch(n, sc, cm, pr, fr, stream)
+    if entry == "noalloc":
+        return L.tr_render_batch_noalloc(n, sc, cm, pr, fr, None, stream)
+    g = C.c_void_p()
+    return L.tr_graph_create(n, sc, cm, pr, fr, None, stream, C.byref(g))
+
+
+def large_fp32(model, tr):
+    """Frames up to the limit in one workgroup per entry, larger ones on
+    persistent waves, through every entry point."""
+    s = tr.Scene(scenegen.tiny_scene(seed=4))
+    for entry in ("render", "batch", "noalloc", "graph"):
+        # (one-pixel rows: a tile each; the last tiles are split in four)
+        for tiles in (LIMIT // 2, LIMIT - 2000000, LIMIT - 600000, LIMIT - 1, LIMIT, 2 * LIMIT - 1, 2 * LIMIT + 1):
+            assert _render(tr, entry, [_job(tr, s, 1, tiles)]) == 0, (entry, tiles, tr.lib().tr_last_error())
+            name, grid, block = hip_model.launches(model)[-1]
+            assert "k_render_wave" in name and grid * block < 2 ** 32
+            assert (grid < tiles) == (tiles >= LIMIT - 600000), (entry, tiles, grid)
+    assert _render(tr, "render", [_job(tr, s, 3860, 4548, aa_samples=256)]) == 0, tr.lib().tr_last_error()
+    assert _render(tr, "batch", [_job(tr, s, 1024, 1024)] * 4096) == 0, tr.lib().tr_last_error()
+
+
+@pytest.mark.parametrize("test", ["large_fp32"])
+def test_launch_sizes(test):
+    hip_model.run("test_host_launch", test)
