@@ -48,6 +48,20 @@ def large_fp32(model, tr):
     assert _render(tr, "batch", [_job(tr, s, 1024, 1024)] * 4096) == 0, tr.lib().tr_last_error()
 
 
-@pytest.mark.parametrize("test", ["large_fp32"])
+def large_fp64(model, tr):
+    """Narrow FP64 frames of 2^26 tiles and more: all entries in launches that
+    the runtime takes."""
+    s = tr.Scene(scenegen.tiny_scene(seed=4))
+    for height in (8 * 5000, 8 * (LIMIT - 1), 8 * LIMIT, 2 ** 31 - 2):
+        before = len(hip_model.launches(model))
+        assert _render(tr, "render", [_job(tr, s, 1, height, "fp64")]) == 0, (height, tr.lib().tr_last_error())
+        grids = [g for n, g, b in hip_model.launches(model)[before:] if "k_render_f64" in n]
+        tiles = (height + 7) // 8
+        split = int(60.0 * tiles ** 0.5)
+        assert tiles <= sum(grids) <= tiles + 3 * split + 4096, (height, grids)
+        assert all(g % 8 == 0 for g in grids)  # (a workgroup's XCD is its number mod 8)
+
+
+@pytest.mark.parametrize("test", ["large_fp32", "large_fp64"])
 def test_launch_sizes(test):
     hip_model.run("test_host_launch", test)
