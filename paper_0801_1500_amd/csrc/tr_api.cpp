@@ -1138,16 +1138,22 @@ static tr_status make_job(const tr_scene *s, const tr_camera *c, const tr_params
 // ------------------------------------------------------ launch resources
 // Per-stream ring of job tables: device table, tile counter and, for tables of
 // more jobs than one launch writes from its arguments, pinned staging that is
-// reusable once the copy from it has run (the device parts are ordered by the
-// stream).
+// reusable once the copy from it has run.  The device parts are ordered by the
+// stream.  One handle is not one stream: hipStreamPerThread is another stream
+// in every thread, so there a launch waits on the device for the one that had
+// its slot last.  (A handle that comes back after hipStreamDestroy brings no
+// work with it: the call waits for the stream, 108 ms with a kernel of that
+// length under way.)
 struct LaunchSlot {
   JobDev *h_jobs = nullptr;
   JobDev *d_jobs = nullptr;
   uint32_t *d_counter = nullptr;  // tile queue counters + stall flag (kQueueWords)
   int32_t cap = 0, h_cap = 0;
   hipEvent_t staged = nullptr;  // the last copy from h_jobs
+  hipEvent_t done = nullptr;    // hipStreamPerThread: the last launch
 };
 struct StreamRing {
+  std::mutex mu;  // held until a launch and its events are enqueued
   LaunchSlot slot[4];
   int next = 0;
 };
@@ -1166,25 +1172,33 @@ static int num_cus() {
   return g_num_cus;
 }
 
-static tr_status acquire_slot(hipStream_t st, int32_t n, LaunchSlot **out) {
+static StreamRing &stream_ring(hipStream_t st) {
   int dev = 0;
   (void)hipGetDevice(&dev);
   std::lock_guard<std::mutex> lk(g_mu);
-  StreamRing &ring = g_rings[{dev, st}];
+  return g_rings[{dev, st}];  // (entries stay where they are)
+}
+
+static bool is_capturing(hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();  // (the default stream, while another stream captures)
+  return false;
+}
+
+// The ring's next slot, with room for n jobs (the ring's lock is held).
+static tr_status next_slot(StreamRing &ring, int32_t n, bool staging, LaunchSlot **out) {
   LaunchSlot &ls = ring.slot[ring.next];
   ring.next = (ring.next + 1) % 4;
   if (ls.cap < n) {
-    if (ls.d_jobs) {  // launches enqueued on the stream may still read it
-      HIP_TRY(hipStreamSynchronize(st));
-      HIP_TRY(hipFree(ls.d_jobs));
-    }
+    if (ls.d_jobs) HIP_TRY(hipFree(ls.d_jobs));  // (waits for the device)
     ls.d_jobs = nullptr;
     ls.cap = 0;
     const int32_t cap = std::max(n, 8);
     HIP_TRY(hipMalloc((void **)&ls.d_jobs, sizeof(JobDev) * cap));
     ls.cap = cap;
   }
-  if (n > trh::kPutJobs) {
+  if (staging) {
     if (!ls.staged) HIP_TRY(hipEventCreateWithFlags(&ls.staged, hipEventDisableTiming));
     HIP_TRY(hipEventSynchronize(ls.staged));  // (at once when never recorded)
     if (ls.h_cap < n) {
@@ -1420,21 +1434,34 @@ static tr_status launch_wave_jobs(std::vector<JobDev> &jobs, const tr_tune &t, u
   const int64_t total = set_queue(jobs.data(), (int32_t)jobs.size());
   if (total == 0) return TR_OK;
   if (total > (int64_t)UINT32_MAX - 1) return fail(TR_EINVAL, "too many tiles in one launch");
+  // (a captured launch has its table written from arguments, which its replays
+  // keep, and leaves no event that the host could not wait for later)
+  const bool capturing = is_capturing(st), several = st == hipStreamPerThread && !capturing;
+  const bool staging = jobs.size() > (size_t)trh::kPutJobs && !capturing;
+  StreamRing &ring = stream_ring(st);
+  std::lock_guard<std::mutex> lk(ring.mu);
   LaunchSlot *ls = nullptr;
-  tr_status rc = acquire_slot(st, (int32_t)jobs.size(), &ls);
+  tr_status rc = next_slot(ring, (int32_t)jobs.size(), staging, &ls);
   if (rc != TR_OK) return rc;
-  if (jobs.size() > (size_t)trh::kPutJobs) {
-    std::memcpy(ls->h_jobs, jobs.data(), sizeof(JobDev) * jobs.size());
-    HIP_TRY(hipMemcpyAsync(ls->d_jobs, ls->h_jobs, sizeof(JobDev) * jobs.size(), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipEventRecord(ls->staged, st));
-  } else {  // (a kernel of 2 us, where a copy is a staging buffer and an event besides)
-    HIP_TRY(trh::launch_put_jobs(jobs.data(), (int32_t)jobs.size(), ls->d_jobs, st));
-  }
-  const trh::WaveLaunch L = wave_launch(jobs.data(), (int32_t)jobs.size(), total, t, stats,
-                                        ls->d_jobs, ls->d_counter);
-  if (L.part_log2 < 0) HIP_TRY(trh::launch_fill_u32(ls->d_counter, trd::kQueueWords, 0u, st));
-  HIP_TRY(trh::launch_render_wave(L, st));
-  return TR_OK;
+  if (several && ls->done) HIP_TRY(hipStreamWaitEvent(st, ls->done, 0));
+  if (several && !ls->done) HIP_TRY(hipEventCreateWithFlags(&ls->done, hipEventDisableTiming));
+  const auto enqueue = [&]() -> tr_status {
+    if (staging) {
+      std::memcpy(ls->h_jobs, jobs.data(), sizeof(JobDev) * jobs.size());
+      HIP_TRY(hipMemcpyAsync(ls->d_jobs, ls->h_jobs, sizeof(JobDev) * jobs.size(), hipMemcpyHostToDevice, st));
+      HIP_TRY(hipEventRecord(ls->staged, st));
+    } else {  // (a kernel of 2 us, where a copy is a staging buffer and an event besides)
+      HIP_TRY(trh::launch_put_jobs(jobs.data(), (int32_t)jobs.size(), ls->d_jobs, st));
+    }
+    const trh::WaveLaunch L = wave_launch(jobs.data(), (int32_t)jobs.size(), total, t, stats,
+                                          ls->d_jobs, ls->d_counter);
+    if (L.part_log2 < 0) HIP_TRY(trh::launch_fill_u32(ls->d_counter, trd::kQueueWords, 0u, st));
+    HIP_TRY(trh::launch_render_wave(L, st));
+    return TR_OK;
+  };
+  rc = enqueue();
+  if (several) HIP_TRY(hipEventRecord(ls->done, st));  // (also after a failed launch: the table was written)
+  return rc;
 }
 
 // --------------------------------------------------------------- renders

@@ -38,7 +38,6 @@ def load():
         getattr(model, f).restype = res
     model.model_capacity.argtypes = [C.c_int, C.c_size_t]
     model.model_capture.argtypes = [C.c_void_p, C.c_int]
-    model.model_reuse_handle.argtypes = [C.c_void_p]
     torch = sys.modules["torch"] = types.ModuleType("torch")  # (the binding loads it first)
     torch.cuda = types.SimpleNamespace(is_available=lambda: True,
                                        current_stream=lambda: types.SimpleNamespace(cuda_stream=None))

@@ -95,8 +95,6 @@ API long model_mallocs() { return mallocs; }
 API void model_fail_sync(int on) { fail_sync = on; }
 API void model_fail_new(int after) { fail_new = after; }
 API void model_capture(void *st, int on) { capturing[(uintptr_t)st] = on != 0; }
-// the handle's stream is destroyed with its work still running, and a new stream gets the handle
-API void model_reuse_handle(void *st) { real.erase({(uintptr_t)st, -1}); }
 API void model_hold(int on) { std::lock_guard<std::recursive_mutex> l(mu); hold = on != 0; held.notify_all(); }
 API long model_staged_changed() { return staged_changed; }
 API long model_pending(int dev) {  // operations of the device that this thread has not waited for

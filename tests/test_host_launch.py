@@ -1,6 +1,9 @@
 """Host side of the render launches, on a model of the HIP runtime (no GPU):
-launch sizes at the runtime's limit of 2^32 work-items per dimension."""
+launch sizes at the runtime's limit of 2^32 work-items per dimension, and the
+order of the accesses to the job tables when equal stream handles are not one
+stream, under capture and with tables that grow."""
 import ctypes as C
+import threading
 
 import pytest
 
@@ -60,6 +63,45 @@ def large_fp64(model, tr):
         split = int(60.0 * tiles ** 0.5)
         assert tiles <= sum(grids) <= tiles + 3 * split + 4096, (height, grids)
         assert all(g % 8 == 0 for g in grids)  # (a workgroup's XCD is its number mod 8)
+
+
+def tables_per_thread_stream(model, tr):
+    """hipStreamPerThread is one handle and another stream in every thread."""
+    s = tr.Scene(scenegen.tiny_scene(seed=4))
+    for n in (1, 3, 5, 20):
+        for rounds in (1, 9, 2):
+            def work():
+                for _ in range(rounds):
+                    assert _render(tr, "batch", [_job(tr, s, 64, 64)] * n, 2) == 0
+            t = threading.Thread(target=work)
+            t.start()
+            t.join()
+    assert model.model_races() == 0, model.model_races()
+
+
+def tables_under_capture(model, tr):
+    """Captured renders wait for nothing on the host and leave nothing behind
+    that a later render could not wait for."""
+    s = tr.Scene(scenegen.tiny_scene(seed=4))
+    for n in (1, 3, 5):
+        for _ in range(5):  # the slots' memory
+            assert _render(tr, "batch", [_job(tr, s, 64, 64)] * 5, 0x5000) == 0
+        model.model_capture(0x5000, 1)
+        for _ in range(5):
+            assert _render(tr, "batch", [_job(tr, s, 64, 64)] * n, 0x5000) == 0, tr.lib().tr_last_error()
+        model.model_capture(0x5000, 0)
+        for _ in range(9):
+            assert _render(tr, "batch", [_job(tr, s, 64, 64)] * n, 0x5000) == 0, tr.lib().tr_last_error()
+    assert model.model_bad_waits() == 0 and model.model_races() == 0
+    model.model_capture(0x6000, 1)  # another stream's capture, as another thread may have under way
+    for _ in range(9):
+        assert _render(tr, "batch", [_job(tr, s, 64, 64)], 0x5000) == 0, tr.lib().tr_last_error()
+    assert model.model_races() == 0
+
+
+@pytest.mark.parametrize("test", ["tables_per_thread_stream", "tables_under_capture"])
+def test_job_tables(test):
+    hip_model.run("test_host_launch", test)
 
 
 @pytest.mark.parametrize("test", ["large_fp32", "large_fp64"])
