@@ -55,9 +55,8 @@ static bool finite3(const double *v) {
 // and giving them back cost 0.25 ms of a 0.7 ms build and destroy, 4 ms for
 // 200,000 objects.  Blocks come in sizes of at most one part in eight more than
 // asked for.  At most kKeepBytes a device are kept, all of them are given back
-// when the device runs out of memory, and a block goes back in only once the
-// device is done with it (the caller synchronises first), so any thread may
-// have it on any stream.
+// when the device runs out of memory, and a block is kept only where its device
+// is done with it, so any thread may have it on any stream.
 constexpr int kMaxDevices = 64;
 constexpr size_t kKeepBytes = (size_t)256 << 20;
 constexpr size_t kKeepHost = 64;  // pinned blocks
@@ -109,8 +108,9 @@ static hipError_t dev_alloc(void **p, size_t bytes) {
   return hipSuccess;
 }
 
-// The device must be done with the block.
-static void dev_free(void *p) {
+// idle: everything that uses the block is known to be done; otherwise it goes
+// to hipFree, which waits for the device.
+static void dev_free(void *p, bool idle) {
   if (!p) return;
   KeptBlocks &b = blocks();
   std::unique_lock<std::mutex> lk(b.mu);
@@ -118,7 +118,7 @@ static void dev_free(void *p) {
   const size_t size = it->second.first;
   const int dev = it->second.second;
   b.live.erase(it);
-  if (b.held[dev] + size <= kKeepBytes) {
+  if (idle && b.held[dev] + size <= kKeepBytes) {
     b.kept[dev].emplace(size, p);
     b.held[dev] += size;
     return;
@@ -163,7 +163,7 @@ static size_t g_stage_cap = 0;
 
 // ------------------------------------------------------------------ scene
 struct tr_scene {
-  int device = 0;
+  uint64_t devices = 0;  // those that were current when it was built or rebuilt (bits)
   int32_t key = 0;
   int64_t n_s = 0, n_c = 0, n_t = 0;
   int32_t n_lights = 0;
@@ -206,13 +206,35 @@ struct tr_scene {
 static int32_t g_scene_key = 0;
 static std::mutex g_mu;
 
+static_assert(kMaxDevices <= 64, "tr_scene::devices has a bit for each");
+static void add_device(tr_scene *s) {
+  int dev = 0;
+  if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices) s->devices |= 1ull << dev;
+}
+
+// Wait for all work on the scene's devices, whichever is current: renders on
+// any stream may use its arrays.
+static hipError_t scene_wait(const tr_scene *s) {
+  int now = 0;
+  hipError_t e = hipGetDevice(&now);
+  for (int dev = 0; e == hipSuccess && dev < kMaxDevices; ++dev) {
+    if (!((s->devices >> dev) & 1u)) continue;
+    if (dev != now) e = hipSetDevice(dev);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (dev != now) (void)hipSetDevice(now);
+  }
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
+}
+
 static void free_scene_arrays(tr_scene *s) {
+  const bool idle = scene_wait(s) == hipSuccess;
   void *ptrs[] = {s->sph64, s->cylA64, s->cylW64, s->cylB64, s->sph32,       s->cylA32,
                   s->cylW32, s->albedo, s->cell_begin, s->refs, s->count, s->scan_scratch,
                   s->bounds_scratch, s->bounds, s->cellinfo, s->dist0, s->dist1, s->wrefs,
                   s->triA64, s->triB64, s->triC64, s->tri32,
                   s->bvh_nodes, s->total64};
-  for (void *p : ptrs) dev_free(p);
+  for (void *p : ptrs) dev_free(p, idle);
   if (s->counted) (void)hipEventDestroy(s->counted);
   host_free(s->h_bounds);  // (h_total is in the same block)
 }
@@ -304,6 +326,7 @@ static void fill_scene_dev(tr_scene *s) {
 // Bounds -> parameters -> count -> scan -> scatter -> sort, from the resident
 // FP64 arrays.  Two blocking readbacks (bounds, reference total).
 static tr_status build_grid_impl(tr_scene *s, hipStream_t st) {
+  add_device(s);
   const int64_t N = s->n_s + s->n_c + s->n_t;
   trh::BuildArgs a{};
   a.n_s = (int32_t)s->n_s;
@@ -335,12 +358,12 @@ static tr_status build_grid_impl(tr_scene *s, hipStream_t st) {
   for (int a = 0; a < 3; ++a) s->org[a] = 0.5 * (s->gp.lo[a] + s->gp.hi[a]);
   const int64_t nc = s->gp.n_cells;
   if (nc + 1 > s->cap_cells) {
-    if (s->cell_begin) HIP_TRY(hipDeviceSynchronize());  // renders on any stream may read them
-    dev_free(s->cell_begin);
-    dev_free(s->count);
-    dev_free(s->cellinfo);
-    dev_free(s->dist0);
-    dev_free(s->dist1);
+    if (s->cell_begin) HIP_TRY(scene_wait(s));
+    dev_free(s->cell_begin, true);
+    dev_free(s->count, true);
+    dev_free(s->cellinfo, true);
+    dev_free(s->dist0, true);
+    dev_free(s->dist1, true);
     s->cell_begin = s->count = nullptr;
     s->cellinfo = nullptr;
     s->dist0 = s->dist1 = nullptr;
@@ -354,8 +377,8 @@ static tr_status build_grid_impl(tr_scene *s, hipStream_t st) {
   }
   const int64_t need_scan = trh::cell_scan_words(nc);
   if (need_scan > s->cap_scan) {
-    if (s->scan_scratch) HIP_TRY(hipDeviceSynchronize());
-    dev_free(s->scan_scratch);
+    if (s->scan_scratch) HIP_TRY(scene_wait(s));
+    dev_free(s->scan_scratch, true);
     s->scan_scratch = nullptr;
     s->cap_scan = 0;
     HIP_TRY(dmalloc(&s->scan_scratch, need_scan));
@@ -408,16 +431,16 @@ static tr_status build_grid_impl(tr_scene *s, hipStream_t st) {
   const int64_t W = R + nc + 1;  // bound on the walk-list total
   const bool fit = early && R <= cap_lists();
   if (R > s->cap_refs) {
-    if (s->refs) HIP_TRY(hipDeviceSynchronize());
-    dev_free(s->refs);
+    if (s->refs) HIP_TRY(scene_wait(s));
+    dev_free(s->refs, true);
     s->refs = nullptr;
     s->cap_refs = 0;
     HIP_TRY(dmalloc(&s->refs, R));
     s->cap_refs = R;
   }
   if (W > s->cap_wrefs) {
-    if (s->wrefs) HIP_TRY(hipDeviceSynchronize());
-    dev_free(s->wrefs);
+    if (s->wrefs) HIP_TRY(scene_wait(s));
+    dev_free(s->wrefs, true);
     s->wrefs = nullptr;
     s->cap_wrefs = 0;
     HIP_TRY(dmalloc(&s->wrefs, W));
@@ -489,7 +512,7 @@ extern "C" tr_status tr_scene_build(const tr_scene_desc *d, void *hip_stream, tr
   }
   hipStream_t st = (hipStream_t)hip_stream;
   tr_scene *s = new tr_scene();
-  (void)hipGetDevice(&s->device);
+  add_device(s);
   {
     std::lock_guard<std::mutex> lk(g_mu);
     s->key = ++g_scene_key;
@@ -512,7 +535,6 @@ extern "C" tr_status tr_scene_build(const tr_scene_desc *d, void *hip_stream, tr
   }
   auto bail = [&](tr_status stt) {
     std::string msg = g_err;
-    (void)hipDeviceSynchronize();  // whatever was enqueued is done with the arrays
     free_scene_arrays(s);
     delete s;
     g_err = msg;
@@ -610,7 +632,7 @@ extern "C" tr_status tr_scene_build(const tr_scene_desc *d, void *hip_stream, tr
     if (e == hipSuccess) e = trh::launch_pack(pk, st);
     const hipError_t es = hipStreamSynchronize(st);  // (also on an error: copies may be under way)
     if (e == hipSuccess) e = es;
-    dev_free(tmp);
+    dev_free(tmp, es == hipSuccess);
     if (e != hipSuccess)
       return bail(fail(e == hipErrorOutOfMemory ? TR_ENOMEM : TR_EDEVICE, "scene upload: %s",
                        hipGetErrorString(e)));
@@ -639,12 +661,13 @@ extern "C" tr_status tr_scene_build_bvh(tr_scene *s, void *hip_stream) {
   if (n >= ((int64_t)1 << 26)) return fail(TR_EUNSUPPORTED, "BVH needs fewer than 2^26 primitives");
   hipStream_t st = (hipStream_t)hip_stream;
   // renders on any stream may still read the old records
-  if (s->bvh_nodes) HIP_TRY(hipDeviceSynchronize());
+  if (s->bvh_nodes) HIP_TRY(scene_wait(s));
+  add_device(s);
   s->bvh_n = 0;
   s->bvh_depth = 0;
   const int64_t n_nodes = n >= 2 ? n - 1 : 0;
   if (s->bvh_nodes && s->bvh_cap != n_nodes) {
-    dev_free(s->bvh_nodes);  // (the device was synchronised above)
+    dev_free(s->bvh_nodes, true);
     s->bvh_nodes = nullptr;
     s->bvh_cap = 0;
   }
@@ -714,10 +737,10 @@ extern "C" tr_status tr_scene_build_bvh(tr_scene *s, void *hip_stream) {
     if (small) read_depth();
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     depth = max_dep + 1;  // internal nodes on the longest root-to-leaf path
-    if (e != hipSuccess) (void)hipDeviceSynchronize();
-    dev_free(base);
+    const bool idle = e == hipSuccess || scene_wait(s) == hipSuccess;
+    dev_free(base, idle);
     if (e != hipSuccess) {
-      dev_free(s->bvh_nodes);
+      dev_free(s->bvh_nodes, idle);
       s->bvh_nodes = nullptr;
       s->bvh_cap = 0;
       return fail(e == hipErrorOutOfMemory ? TR_ENOMEM : TR_EDEVICE, "BVH build: %s", hipGetErrorString(e));
@@ -984,7 +1007,6 @@ extern "C" tr_status tr_scene_walk_arrays(const tr_scene *s, int32_t *cellinfo, 
 
 extern "C" void tr_scene_destroy(tr_scene *s) {
   if (!s) return;
-  (void)hipDeviceSynchronize();
   free_scene_arrays(s);
   delete s;
 }

@@ -1,0 +1,59 @@
+"""Scene memory on a model of the HIP runtime (no GPU): freed blocks are kept
+for the next scene only when nothing can still be using them."""
+import ctypes as C
+
+import pytest
+
+import hip_model
+import scenegen
+from test_host_launch import _job, _render
+
+
+def _scene(tr, seed=4, n=64):
+    return tr.Scene(scenegen.tiny_scene(seed=seed, n=n))
+
+
+def other_device(model, tr):
+    """A scene destroyed or rebuilt while another device is current: its own
+    device is waited for before its blocks can go to another scene."""
+    hip = C.CDLL(hip_model.LIB)
+    for what in ("destroy", "rebuild", "bvh"):
+        hip.hipSetDevice(0)
+        s = _scene(tr)
+        s.build_bvh()
+        assert _render(tr, "render", [_job(tr, s, 64, 64)]) == 0
+        assert model.model_pending(0) > 0
+        hip.hipSetDevice(1)
+        if what == "destroy":
+            s.destroy()
+        elif what == "rebuild":
+            s.rebuild(cells_per_prim=200000.0)  # (a larger grid: its old blocks are freed)
+        else:
+            s.build_bvh()
+        assert model.model_pending(0) == 0, what
+        now = C.c_int(-1)
+        hip.hipGetDevice(C.byref(now))
+        assert now.value == 1
+        hip.hipSetDevice(0)
+        s.destroy()
+
+
+def failed_wait(model, tr):
+    """Where the device cannot be waited for (a capture under way), blocks are
+    given to the runtime, which waits by itself, and none are kept."""
+    s = _scene(tr)
+    s.destroy()
+    held, frees = model.model_used(0), model.model_frees()
+    s = _scene(tr)
+    assert model.model_used(0) == held  # (the same blocks again)
+    model.model_fail_sync(1)
+    s.destroy()
+    model.model_fail_sync(0)
+    assert model.model_frees() - frees >= 20  # (what is left: the upload's block, idle since)
+    assert model.model_used(0) < held / 8, model.model_used(0)
+    assert model.model_misuse() == 0
+
+
+@pytest.mark.parametrize("test", ["other_device", "failed_wait"])
+def test_blocks_wait_for_their_device(test):
+    hip_model.run("test_host_memory", test)
