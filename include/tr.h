@@ -345,8 +345,9 @@ tr_status tr_scene_walk_arrays(const tr_scene *scene, int32_t *cellinfo, uint32_
 
 /* Free the scene's device memory.  The caller guarantees no enqueued work
  * still uses it (the call synchronises the device before freeing).  Up to
- * 256 MB of freed blocks per device stay with the library for the next scene,
- * until the device runs out of memory. */
+ * 256 MB of freed blocks per device stay with the library for the next scene;
+ * they are given back when a device allocation of the library (a scene, a
+ * workspace, a graph) finds the device out of memory. */
 void tr_scene_destroy(tr_scene *scene);
 
 /* ---------------------------------------------------------------- render */

@@ -80,6 +80,27 @@ static size_t block_size(size_t n) {
   return (n + step - 1) / step * step;
 }
 
+// Memory of the current device, from the runtime.  With nothing left the kept
+// blocks are given back first: every device allocation of this file goes
+// through here.
+static hipError_t device_malloc(void **p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e != hipErrorOutOfMemory) return e;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev >= kMaxDevices) return e;
+  KeptBlocks &b = blocks();
+  std::multimap<size_t, void *> kept;
+  {
+    std::lock_guard<std::mutex> lk(b.mu);
+    kept.swap(b.kept[dev]);
+    b.held[dev] = 0;
+  }
+  if (kept.empty()) return e;
+  (void)hipGetLastError();
+  for (const auto &k : kept) (void)hipFree(k.second);
+  return hipMalloc(p, bytes);
+}
+
 static hipError_t dev_alloc(void **p, size_t bytes) {
   KeptBlocks &b = blocks();
   const size_t size = block_size(bytes);
@@ -94,15 +115,10 @@ static hipError_t dev_alloc(void **p, size_t bytes) {
     b.kept[dev].erase(it);
     b.held[dev] -= size;
   } else {
-    e = hipMalloc(p, size);
-    if (e == hipErrorOutOfMemory && b.held[dev] > 0) {
-      (void)hipGetLastError();
-      for (const auto &k : b.kept[dev]) (void)hipFree(k.second);
-      b.kept[dev].clear();
-      b.held[dev] = 0;
-      e = hipMalloc(p, size);
-    }
+    lk.unlock();
+    e = device_malloc(p, size);
     if (e != hipSuccess) return e;
+    lk.lock();
   }
   b.live[*p] = {size, dev};
   return hipSuccess;
@@ -1217,7 +1233,7 @@ static tr_status next_slot(StreamRing &ring, int32_t n, bool staging, LaunchSlot
     ls.d_jobs = nullptr;
     ls.cap = 0;
     const int32_t cap = std::max(n, 8);
-    HIP_TRY(hipMalloc((void **)&ls.d_jobs, sizeof(JobDev) * cap));
+    HIP_TRY(device_malloc((void **)&ls.d_jobs, sizeof(JobDev) * cap));
     ls.cap = cap;
   }
   if (staging) {
@@ -1231,7 +1247,7 @@ static tr_status next_slot(StreamRing &ring, int32_t n, bool staging, LaunchSlot
       ls.h_cap = ls.cap;
     }
   }
-  if (!ls.d_counter) HIP_TRY(hipMalloc((void **)&ls.d_counter, trd::kQueueWords * sizeof(uint32_t)));
+  if (!ls.d_counter) HIP_TRY(device_malloc((void **)&ls.d_counter, trd::kQueueWords * sizeof(uint32_t)));
   *out = &ls;
   return TR_OK;
 }
@@ -1303,7 +1319,7 @@ static tr_status aa_workspace(hipStream_t st, int64_t n_floats, float **out) {
       w.buf = nullptr;
       w.cap = 0;
     }
-    HIP_TRY(hipMalloc((void **)&w.buf, (size_t)n_floats * sizeof(float)));
+    HIP_TRY(device_malloc((void **)&w.buf, (size_t)n_floats * sizeof(float)));
     w.cap = n_floats;
   }
   *out = w.buf;
@@ -1749,7 +1765,7 @@ extern "C" tr_status tr_frame_encode_tga(const uint8_t *rgb8, int32_t width, int
       w.rows = nullptr;
       w.cap = 0;
     }
-    HIP_TRY(hipMalloc((void **)&w.rows, (2 * (size_t)height + 1) * sizeof(int64_t)));
+    HIP_TRY(device_malloc((void **)&w.rows, (2 * (size_t)height + 1) * sizeof(int64_t)));
     w.cap = height;
   }
   if (!w.h_total) HIP_TRY(hipHostMalloc((void **)&w.h_total, sizeof(int64_t), hipHostMallocDefault));
@@ -1913,8 +1929,8 @@ extern "C" tr_status tr_graph_create(int32_t n, const tr_scene *const *scenes, c
   g->total_tiles = total;
   hipStream_t st = (hipStream_t)hip_stream;
   hipError_t e = hipHostMalloc((void **)&g->h_jobs, sizeof(JobDev) * n, hipHostMallocDefault);
-  if (e == hipSuccess) e = hipMalloc((void **)&g->d_jobs, sizeof(JobDev) * n);
-  if (e == hipSuccess) e = hipMalloc((void **)&g->d_counter, trd::kQueueWords * sizeof(uint32_t));
+  if (e == hipSuccess) e = device_malloc((void **)&g->d_jobs, sizeof(JobDev) * n);
+  if (e == hipSuccess) e = device_malloc((void **)&g->d_counter, trd::kQueueWords * sizeof(uint32_t));
   if (e == hipSuccess) e = hipEventCreateWithFlags(&g->staged, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&g->launched, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventRecord(g->staged, st);
@@ -2213,10 +2229,10 @@ extern "C" tr_status tr_autotune(const tr_scene *s, const tr_camera *c, const tr
     if (e1) (void)hipEventDestroy(e1);
   };
   {
-    hipError_t e = hipMalloc((void **)&rgb_ref, px * 12);
-    if (e == hipSuccess) e = hipMalloc((void **)&rgb, px * 12);
-    if (e == hipSuccess) e = hipMalloc((void **)&hid_ref, px * 4);
-    if (e == hipSuccess) e = hipMalloc((void **)&hid, px * 4);
+    hipError_t e = device_malloc((void **)&rgb_ref, px * 12);
+    if (e == hipSuccess) e = device_malloc((void **)&rgb, px * 12);
+    if (e == hipSuccess) e = device_malloc((void **)&hid_ref, px * 4);
+    if (e == hipSuccess) e = device_malloc((void **)&hid, px * 4);
     if (e == hipSuccess) e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
     if (e != hipSuccess) {

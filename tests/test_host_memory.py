@@ -54,6 +54,46 @@ def failed_wait(model, tr):
     assert model.model_misuse() == 0
 
 
+def out_of_memory(model, tr):
+    """Every device allocation of the library gets the kept blocks back when
+    the device has nothing left."""
+    L = tr.lib()
+    s = _scene(tr)
+
+    def aa():
+        return _render(tr, "render", [_job(tr, s, 300, 300, aa_samples=4)], 0x5000)
+
+    def table():
+        return _render(tr, "batch", [_job(tr, s, 64, 64)] * 300, 0x6000)
+
+    def graph():
+        return _render(tr, "graph", [_job(tr, s, 64, 64)] * 30)
+
+    def targa():
+        size = C.c_int64()
+        img, out = (C.c_uint8 * 48)(), (C.c_uint8 * 256)()
+        return L.tr_frame_encode_tga(img, 4, 4, out, 256, C.byref(size), 0x7000)
+
+    def scene():
+        _scene(tr, n=700)
+        return 0
+
+    for op in (aa, table, graph, targa, scene):
+        _scene(tr, n=40000).destroy()
+        held = model.model_used(0)
+        assert held > 4 << 20
+        model.model_capacity(0, held)
+        assert op() == 0, (op.__name__, L.tr_last_error())
+        assert model.model_used(0) < held
+        model.model_capacity(0, 1 << 50)
+    assert model.model_misuse() == 0
+
+
+@pytest.mark.parametrize("test", ["out_of_memory"])
+def test_kept_blocks_are_given_back(test):
+    hip_model.run("test_host_memory", test)
+
+
 @pytest.mark.parametrize("test", ["other_device", "failed_wait"])
 def test_blocks_wait_for_their_device(test):
     hip_model.run("test_host_memory", test)
