@@ -59,14 +59,22 @@ static bool finite3(const double *v) {
 // is done with it, so any thread may have it on any stream.
 constexpr int kMaxDevices = 64;
 constexpr size_t kKeepBytes = (size_t)256 << 20;
-constexpr size_t kKeepHost = 64;  // pinned blocks
+constexpr int kKeepBlocks = 256;
+constexpr int kKeepHost = 64;  // pinned blocks
 
+// (fixed arrays: giving a block back allocates nothing and cannot fail)
 struct KeptBlocks {
+  struct Block {
+    void *p;
+    size_t size;
+  };
   std::mutex mu;
-  std::multimap<size_t, void *> kept[kMaxDevices];  // by size
-  size_t held[kMaxDevices] = {};
+  Block kept[kMaxDevices][kKeepBlocks];  // in the order they were freed
+  int n[kMaxDevices] = {};
+  size_t held[kMaxDevices] = {};         // bytes
   std::unordered_map<void *, std::pair<size_t, int>> live;  // size, device
-  std::vector<void *> host;                                 // pinned, kHostBlock bytes each
+  void *host[kKeepHost];                 // pinned, kHostBlock bytes each
+  int n_host = 0;
 };
 static KeptBlocks &blocks() {  // (never destroyed: the driver's own teardown comes first)
   static KeptBlocks *b = new KeptBlocks();
@@ -89,15 +97,18 @@ static hipError_t device_malloc(void **p, size_t bytes) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev >= kMaxDevices) return e;
   KeptBlocks &b = blocks();
-  std::multimap<size_t, void *> kept;
+  KeptBlocks::Block kept[kKeepBlocks];
+  int n;
   {
     std::lock_guard<std::mutex> lk(b.mu);
-    kept.swap(b.kept[dev]);
+    n = b.n[dev];
+    std::copy(b.kept[dev], b.kept[dev] + n, kept);
+    b.n[dev] = 0;
     b.held[dev] = 0;
   }
-  if (kept.empty()) return e;
+  if (n == 0) return e;
   (void)hipGetLastError();
-  for (const auto &k : kept) (void)hipFree(k.second);
+  for (int k = 0; k < n; ++k) (void)hipFree(kept[k].p);
   return hipMalloc(p, bytes);
 }
 
@@ -108,19 +119,27 @@ static hipError_t dev_alloc(void **p, size_t bytes) {
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev >= kMaxDevices) return hipErrorInvalidDevice;
-  std::unique_lock<std::mutex> lk(b.mu);
-  const auto it = b.kept[dev].find(size);
-  if (it != b.kept[dev].end()) {
-    *p = it->second;
-    b.kept[dev].erase(it);
-    b.held[dev] -= size;
-  } else {
-    lk.unlock();
-    e = device_malloc(p, size);
-    if (e != hipSuccess) return e;
-    lk.lock();
+  *p = nullptr;
+  {
+    std::lock_guard<std::mutex> lk(b.mu);
+    KeptBlocks::Block *const first = b.kept[dev];
+    for (int k = b.n[dev] - 1; k >= 0 && !*p; --k) {
+      if (first[k].size != size) continue;
+      *p = first[k].p;
+      std::copy(first + k + 1, first + b.n[dev]--, first + k);
+      b.held[dev] -= size;
+    }
   }
-  b.live[*p] = {size, dev};
+  if (!*p) e = device_malloc(p, size);
+  if (e != hipSuccess) return e;
+  try {
+    std::lock_guard<std::mutex> lk(b.mu);
+    b.live[*p] = {size, dev};
+  } catch (const std::bad_alloc &) {
+    (void)hipFree(*p);
+    *p = nullptr;
+    return hipErrorOutOfMemory;
+  }
   return hipSuccess;
 }
 
@@ -134,8 +153,8 @@ static void dev_free(void *p, bool idle) {
   const size_t size = it->second.first;
   const int dev = it->second.second;
   b.live.erase(it);
-  if (idle && b.held[dev] + size <= kKeepBytes) {
-    b.kept[dev].emplace(size, p);
+  if (idle && b.held[dev] + size <= kKeepBytes && b.n[dev] < kKeepBlocks) {
+    b.kept[dev][b.n[dev]++] = {p, size};
     b.held[dev] += size;
     return;
   }
@@ -148,9 +167,8 @@ static hipError_t host_alloc(void **p) {
   KeptBlocks &b = blocks();
   {
     std::lock_guard<std::mutex> lk(b.mu);
-    if (!b.host.empty()) {
-      *p = b.host.back();
-      b.host.pop_back();
+    if (b.n_host > 0) {
+      *p = b.host[--b.n_host];
       return hipSuccess;
     }
   }
@@ -161,8 +179,8 @@ static void host_free(void *p) {
   KeptBlocks &b = blocks();
   {
     std::lock_guard<std::mutex> lk(b.mu);
-    if (b.host.size() < kKeepHost) {
-      b.host.push_back(p);
+    if (b.n_host < kKeepHost) {
+      b.host[b.n_host++] = p;
       return;
     }
   }
@@ -594,11 +612,12 @@ extern "C" tr_status tr_scene_build(const tr_scene_desc *d, void *hip_stream, tr
       size_t bytes, at;
       const void **dst;
     };
-    std::vector<Part> parts;
+    Part parts[14];
+    int n_parts = 0;
     size_t total = 0;
     const auto part = [&](const void *src, int64_t bytes, const void **dst) {
       if (!src || bytes == 0) return;
-      parts.push_back(Part{src, (size_t)bytes, total, dst});
+      parts[n_parts++] = Part{src, (size_t)bytes, total, dst};
       total += ((size_t)bytes + 255) & ~(size_t)255;
     };
     part(d->sph_center, 24 * s->n_s, (const void **)&pk.sc);
@@ -631,7 +650,8 @@ extern "C" tr_status tr_scene_build(const tr_scene_desc *d, void *hip_stream, tr
       }
     }
     const bool staged = stage.owns_lock() && g_stage_cap >= total;
-    for (const Part &q : parts) {
+    for (int k = 0; k < n_parts; ++k) {
+      const Part &q = parts[k];
       *q.dst = tmp + q.at;
       if (staged) std::memcpy(g_stage + q.at, q.src, q.bytes);
       else if (e == hipSuccess) e = hipMemcpyAsync(tmp + q.at, q.src, q.bytes, hipMemcpyHostToDevice, st);

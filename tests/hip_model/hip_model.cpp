@@ -9,6 +9,7 @@
 //     reads them) that nothing orders: no stream, event or wait between them;
 //   - per device, work that nothing has waited for, bytes allocated, capacity;
 //   - waits on events during a capture, and on events recorded in one.
+#include <dlfcn.h>
 #include <sys/mman.h>
 
 #include <cstdint>
@@ -93,7 +94,8 @@ API long model_misuse() { return misuse; }
 API long model_frees() { return frees; }
 API long model_mallocs() { return mallocs; }
 API void model_fail_sync(int on) { fail_sync = on; }
-API void model_fail_new(int after) { fail_new = after; }
+API void model_fail_new(int after) { fail_new = after; }  // the one after so many; -1 none
+API int model_failed_new() { return fail_new < 0; }
 API void model_capture(void *st, int on) { capturing[(uintptr_t)st] = on != 0; }
 API void model_hold(int on) { std::lock_guard<std::recursive_mutex> l(mu); hold = on != 0; held.notify_all(); }
 API long model_staged_changed() { return staged_changed; }
@@ -111,8 +113,9 @@ API int model_log(int i, char *out, int cap) {  // the i-th launch as "name grid
 }
 
 void *operator new(size_t n) {
-  if (fail_new == 0) throw std::bad_alloc();
-  if (fail_new > 0) --fail_new;
+  Dl_info who;  // (only the library's own allocations count and fail)
+  if (fail_new >= 0 && dladdr(__builtin_return_address(0), &who) && std::strstr(who.dli_fname, "libtr.so") && fail_new-- == 0)
+    throw std::bad_alloc();
   void *p = std::malloc(n ? n : 1);
   if (!p) throw std::bad_alloc();
   return p;

@@ -89,6 +89,39 @@ def out_of_memory(model, tr):
     assert model.model_misuse() == 0
 
 
+def host_out_of_memory(model, tr):
+    """No C++ exception leaves a scene call when the host runs out of memory
+    while a block is taken or given back."""
+    _scene(tr).destroy()
+    for k in range(2000):
+        model.model_fail_new(k + 1)  # (the scene itself is made)
+        try:
+            s = _scene(tr)
+        except tr.TRError as e:
+            assert e.status == tr.TR_ENOMEM, str(e)
+            s = None
+        done = not model.model_failed_new()
+        model.model_fail_new(-1)
+        if s:
+            s.destroy()
+        if done:
+            break
+    assert done and k > 20
+    for k in range(2000):
+        s = _scene(tr)
+        model.model_fail_new(k)
+        s.destroy()
+        done = not model.model_failed_new()
+        model.model_fail_new(-1)
+        if done:
+            break
+    assert done and model.model_misuse() == 0
+
+
+def test_no_exception_leaves():
+    hip_model.run("test_host_memory", "host_out_of_memory")
+
+
 @pytest.mark.parametrize("test", ["out_of_memory"])
 def test_kept_blocks_are_given_back(test):
     hip_model.run("test_host_memory", test)
