@@ -54,9 +54,10 @@ static bool finite3(const double *v) {
 // scene: a protein's scene is some 30 blocks, and taking them from the driver
 // and giving them back cost 0.25 ms of a 0.7 ms build and destroy, 4 ms for
 // 200,000 objects.  Blocks come in sizes of at most one part in eight more than
-// asked for.  At most kKeepBytes a device are kept, all of them are given back
-// when the device runs out of memory, and a block is kept only where its device
-// is done with it, so any thread may have it on any stream.
+// asked for.  At most kKeepBytes a device are kept, the last freed (older ones
+// make room: scenes of sizes that do not come back must not fill the list), all
+// are given back when the device runs out of memory, and a block is kept only
+// where its device is done with it, so any thread may have it on any stream.
 constexpr int kMaxDevices = 64;
 constexpr size_t kKeepBytes = (size_t)256 << 20;
 constexpr int kKeepBlocks = 256;
@@ -153,13 +154,24 @@ static void dev_free(void *p, bool idle) {
   const size_t size = it->second.first;
   const int dev = it->second.second;
   b.live.erase(it);
-  if (idle && b.held[dev] + size <= kKeepBytes && b.n[dev] < kKeepBlocks) {
-    b.kept[dev][b.n[dev]++] = {p, size};
+  KeptBlocks::Block out[kKeepBlocks + 1];  // what goes back to the runtime
+  int n_out = 0;
+  if (idle && size <= kKeepBytes) {
+    KeptBlocks::Block *const first = b.kept[dev];
+    while (b.held[dev] + size > kKeepBytes || b.n[dev] - n_out == kKeepBlocks) {
+      b.held[dev] -= first[n_out].size;
+      out[n_out] = first[n_out];
+      ++n_out;
+    }
+    std::copy(first + n_out, first + b.n[dev], first);
+    b.n[dev] -= n_out;
+    first[b.n[dev]++] = {p, size};
     b.held[dev] += size;
-    return;
+  } else {
+    out[n_out++] = {p, size};
   }
   lk.unlock();
-  (void)hipFree(p);
+  for (int k = 0; k < n_out; ++k) (void)hipFree(out[k].p);
 }
 
 constexpr size_t kHostBlock = 128;

@@ -118,6 +118,27 @@ def host_out_of_memory(model, tr):
     assert done and model.model_misuse() == 0
 
 
+def changing_sizes(model, tr):
+    """Blocks of sizes that do not come back make room for later ones: after
+    any mix of scenes the next of a size finds the last one's blocks, and no
+    more is kept than the limit."""
+    for k in range(40):  # some 500 blocks of different sizes, 300 MB
+        _scene(tr, n=1000 + 1700 * k).destroy()
+        assert model.model_used(0) <= 256 << 20
+    for _ in range(2):
+        _scene(tr, n=20000).destroy()
+    n = model.model_mallocs()
+    for _ in range(3):
+        s = _scene(tr, n=20000)
+        s.destroy()
+    assert model.model_mallocs() == n, model.model_mallocs() - n
+    assert model.model_misuse() == 0
+
+
+def test_kept_blocks_follow_the_scenes():
+    hip_model.run("test_host_memory", "changing_sizes")
+
+
 def test_no_exception_leaves():
     hip_model.run("test_host_memory", "host_out_of_memory")
 
