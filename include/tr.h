@@ -293,7 +293,9 @@ tr_status tr_scene_build_bvh(tr_scene *scene, void *hip_stream);
 tr_status tr_scene_bvh_nodes(const tr_scene *scene, float *nodes, int64_t *n_nodes,
                              int32_t *depth, void *hip_stream);
 
-/* Device bytes held by the scene (arrays + grid). */
+/* Device bytes held by the scene: its arrays, grid and BVH, in the block sizes
+ * they were taken in (an eighth more than their contents at most, 256 bytes at
+ * least). */
 tr_status tr_scene_footprint(const tr_scene *scene, size_t *bytes);
 
 /* Grid shape: lo/hi bounds, resolution, reference count, and the grid's

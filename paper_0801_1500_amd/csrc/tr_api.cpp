@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
@@ -235,7 +236,6 @@ struct tr_scene {
   // device: [0] reference total of the count pass, [1] bounding radius (FP64 bits)
   unsigned long long *total64 = nullptr;
   int64_t cap_cells = 0, cap_refs = 0, cap_scan = 0, cap_wrefs = 0;
-  size_t bytes_arrays = 0;
   // pinned readback
   double *h_bounds = nullptr;
   hipEvent_t counted = nullptr;  // the reference total is in h_total
@@ -273,14 +273,15 @@ static hipError_t scene_wait(const tr_scene *s) {
   return e;
 }
 
+static std::array<void *, 24> scene_blocks(const tr_scene *s) {
+  return {s->sph64, s->cylA64, s->cylW64, s->cylB64, s->sph32, s->cylA32, s->cylW32, s->albedo,
+          s->cell_begin, s->refs, s->count, s->scan_scratch, s->bounds_scratch, s->bounds, s->cellinfo,
+          s->dist0, s->dist1, s->wrefs, s->triA64, s->triB64, s->triC64, s->tri32, s->bvh_nodes, s->total64};
+}
+
 static void free_scene_arrays(tr_scene *s) {
   const bool idle = scene_wait(s) == hipSuccess;
-  void *ptrs[] = {s->sph64, s->cylA64, s->cylW64, s->cylB64, s->sph32,       s->cylA32,
-                  s->cylW32, s->albedo, s->cell_begin, s->refs, s->count, s->scan_scratch,
-                  s->bounds_scratch, s->bounds, s->cellinfo, s->dist0, s->dist1, s->wrefs,
-                  s->triA64, s->triB64, s->triC64, s->tri32,
-                  s->bvh_nodes, s->total64};
-  for (void *p : ptrs) dev_free(p, idle);
+  for (void *p : scene_blocks(s)) dev_free(p, idle);
   if (s->counted) (void)hipEventDestroy(s->counted);
   host_free(s->h_bounds);  // (h_total is in the same block)
 }
@@ -611,8 +612,6 @@ extern "C" tr_status tr_scene_build(const tr_scene_desc *d, void *hip_stream, tr
   if (e != hipSuccess)
     return bail(fail(e == hipErrorOutOfMemory ? TR_ENOMEM : TR_EDEVICE, "scene allocation: %s",
                      hipGetErrorString(e)));
-  s->bytes_arrays = (size_t)s->n_s * (32 + 16) + (size_t)s->n_c * (3 * 32 + 3 * 16) +
-                    (size_t)s->n_t * (3 * 32 + 3 * 16) + (size_t)N * 16;
   // upload the caller's arrays to one temporary block, then pack
   if (N > 0) {
     trh::PackArgs pk{};
@@ -822,9 +821,11 @@ extern "C" tr_status tr_scene_set_max_skip(tr_scene *s, int32_t max_skip, void *
 
 extern "C" tr_status tr_scene_footprint(const tr_scene *s, size_t *bytes) {
   if (!s || !bytes) return fail(TR_EINVAL, "tr_scene_footprint: NULL argument");
-  *bytes = s->bytes_arrays + (size_t)s->cap_cells * (8 + sizeof(trd::CellInfo) + 2) +
-           (size_t)s->cap_refs * 4 + (size_t)s->cap_wrefs * 4 +
-           (size_t)s->cap_scan * 4;
+  *bytes = 0;
+  KeptBlocks &b = blocks();
+  std::lock_guard<std::mutex> lk(b.mu);
+  for (void *p : scene_blocks(s))
+    if (p) *bytes += b.live.find(p)->second.first;
   return TR_OK;
 }
 

@@ -135,6 +135,24 @@ def changing_sizes(model, tr):
     assert model.model_misuse() == 0
 
 
+def footprint(model, tr):
+    """tr_scene_footprint is what the scene takes from the device."""
+    for n, cells in ((1, 0.0), (64, 0.0), (5000, 0.0), (5000, 3.0)):
+        for bvh in (False, True):
+            s = tr.Scene(scenegen.tiny_scene(seed=4, n=n), cells_per_prim=cells)
+            if bvh:
+                s.build_bvh()
+            used, held = model.model_used(0), s.footprint()
+            model.model_fail_sync(1)  # (so that its blocks are freed, not kept)
+            s.destroy()
+            model.model_fail_sync(0)
+            assert held == used - model.model_used(0), (n, bvh, held, used - model.model_used(0))
+
+
+def test_footprint():
+    hip_model.run("test_host_memory", "footprint")
+
+
 def test_kept_blocks_follow_the_scenes():
     hip_model.run("test_host_memory", "changing_sizes")
 
