@@ -51,7 +51,7 @@ int n_threads;
 thread_local int device, last_error, tid = -1;
 thread_local Clock host;  // what this thread has waited for
 thread_local struct { Dim3 g, b; size_t sh; void *st; } cfg;
-bool hold;
+int hold;  // 1: the next copy is held, 2: one is
 std::condition_variable_any held;
 long staged_changed;
 
@@ -97,7 +97,9 @@ API void model_fail_sync(int on) { fail_sync = on; }
 API void model_fail_new(int after) { fail_new = after; }  // the one after so many; -1 none
 API int model_failed_new() { return fail_new < 0; }
 API void model_capture(void *st, int on) { capturing[(uintptr_t)st] = on != 0; }
-API void model_hold(int on) { std::lock_guard<std::recursive_mutex> l(mu); hold = on != 0; held.notify_all(); }
+API void model_hold_copy() { std::lock_guard<std::recursive_mutex> l(mu); hold = 1; }
+API void model_await_held() { std::unique_lock<std::recursive_mutex> l(mu); held.wait(l, [] { return hold == 2; }); }
+API void model_release_copy() { std::lock_guard<std::recursive_mutex> l(mu); hold = 0; held.notify_all(); }
 API long model_staged_changed() { return staged_changed; }
 API long model_pending(int dev) {  // operations of the device that this thread has not waited for
   std::lock_guard<std::recursive_mutex> l(mu);
@@ -225,16 +227,12 @@ API int hipMemcpyAsync(void *d, const void *s, size_t n, int, void *st) {
   int r;
   const long id = enqueue(st, r);
   if (tables.count((uintptr_t)d)) touch((uintptr_t)d, r, id, true);
-  if (hold) {  // one copy waits here: its source must not change meanwhile
-    hold = false;
+  if (hold == 1) {  // this copy waits for its release: its source must not change meanwhile
+    hold = 2;
+    held.notify_all();
     std::vector<char> before((const char *)s, (const char *)s + n);
-    hold = true;
-    static bool taken = false;
-    if (!taken) {
-      taken = true;
-      held.wait(l, [] { return !hold; });
-      if (std::memcmp(before.data(), s, n)) ++staged_changed;
-    }
+    held.wait(l, [] { return hold == 0; });
+    if (std::memcmp(before.data(), s, n)) ++staged_changed;
   }
   std::memcpy(d, s, n);
   return kOk;

@@ -1,6 +1,8 @@
 """Scene memory on a model of the HIP runtime (no GPU): freed blocks are kept
-for the next scene only when nothing can still be using them."""
+for the next scene only when nothing can still be using them, they are given
+back when memory runs out, and one builder at a time has the staging block."""
 import ctypes as C
+import threading
 
 import pytest
 
@@ -147,6 +149,26 @@ def footprint(model, tr):
             s.destroy()
             model.model_fail_sync(0)
             assert held == used - model.model_used(0), (n, bvh, held, used - model.model_used(0))
+
+
+def two_builders(model, tr):
+    """A build whose upload is under way keeps the staging block: others copy
+    array by array, and neither sees the other's arrays.  Nor does a build of
+    more than the block's 8 MB wait for it."""
+    _scene(tr).destroy()
+    model.model_hold_copy()
+    t = threading.Thread(target=lambda: _scene(tr, seed=1, n=3000))
+    t.start()
+    model.model_await_held()
+    _scene(tr, seed=2, n=3000)
+    _scene(tr, seed=3, n=300000)
+    model.model_release_copy()
+    t.join()
+    assert model.model_staged_changed() == 0 and model.model_misuse() == 0
+
+
+def test_two_builders():
+    hip_model.run("test_host_memory", "two_builders")
 
 
 def test_footprint():
