@@ -560,6 +560,16 @@ tr_status tr_measure_fp32_peak(void *hip_stream, double *tflops, double *clock_m
 tr_status tr_debug_philox(int64_t n, const uint32_t *ctr, const uint32_t *key, uint32_t *out,
                           void *hip_stream);
 
+/* How a launch of one workgroup per entry deals its tiles (host only; the
+ * functions the launches and kernels use): n_jobs frames of tiles_x[i] by
+ * tiles_y[i] tiles, whole, or (ranges != 0) as ranges of as many row-major
+ * tiles.  For each workgroup b below min(capacity, the returned number):
+ * out[5b..5b+4] = job (-1: none, past the last tile), tile column, tile row,
+ * part and number of parts its tile is split in.  Returns the workgroups of the
+ * launch, or -1 on invalid arguments and where persistent waves take over. */
+int64_t tr_debug_entries(int32_t n_jobs, const int32_t *tiles_x, const int32_t *tiles_y,
+                         int32_t ranges, int64_t capacity, int32_t *out);
+
 /* AO directions as the FP32 kernel draws them: for each i, normal
  * n[3i..3i+2] (unit), pixel pix[i], sample s[i] -> w[3i..3i+2].  Device
  * pointers. */

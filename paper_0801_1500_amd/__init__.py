@@ -128,6 +128,7 @@ def lib():
         "tr_default_tune": ([C.POINTER(Tune)], st),
         "tr_measure_fp32_peak": ([vp, C.POINTER(C.c_double), C.POINTER(C.c_double),
                                   C.POINTER(i32)], st),
+        "tr_debug_entries": ([i32, vp, vp, i32, i64, vp], i64),
         "tr_debug_philox": ([i64, vp, vp, vp, vp], st),
         "tr_debug_ao_dirs": ([i64, vp, vp, vp, C.c_uint32, C.c_uint64, vp, vp], st),
         "tr_last_error": ([], C.c_char_p),

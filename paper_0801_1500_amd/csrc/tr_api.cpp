@@ -2386,6 +2386,41 @@ extern "C" tr_status tr_autotune(const tr_scene *s, const tr_camera *c, const tr
 }
 
 // ------------------------------------------------------------------ debug
+extern "C" int64_t tr_debug_entries(int32_t n_jobs, const int32_t *tiles_x, const int32_t *tiles_y,
+                                    int32_t ranges, int64_t capacity, int32_t *out) {
+  if (n_jobs < 1 || !tiles_x || !tiles_y || capacity < 0 || (!out && capacity > 0)) return -1;
+  int64_t total = 0;
+  for (int32_t k = 0; k < n_jobs; ++k) {
+    if (tiles_x[k] < 1 || tiles_y[k] < 1) return -1;
+    total += (int64_t)tiles_x[k] * tiles_y[k];
+  }
+  const trh::Groups g = trh::split_groups(total, n_jobs, !ranges, true);
+  if (g.workgroups > trh::kMaxWorkgroups) return -1;
+  for (int64_t b = 0; b < g.workgroups && b < capacity; ++b) {
+    int32_t *o = out + 5 * b;
+    const int64_t entry = trd::group_entry((uint32_t)b, g.whole, g.part_log2, g.chunk_log2, total);
+    int64_t t = entry >> 7;
+    int32_t k = -1;
+    if (entry >= 0)
+      for (k = 0; t >= (int64_t)tiles_x[k] * tiles_y[k]; ++k) t -= (int64_t)tiles_x[k] * tiles_y[k];
+    o[0] = k;
+    o[1] = o[2] = o[3] = 0;
+    o[4] = 1;
+    if (k < 0) continue;
+    if (g.chunk_log2) {
+      trd::block_tile((uint32_t)t, (uint32_t)tiles_x[k], (uint32_t)tiles_y[k], g.chunk_log2, o[1], o[2]);
+    } else {
+      o[1] = (int32_t)(t % tiles_x[k]);
+      o[2] = (int32_t)(t / tiles_x[k]);
+    }
+    if (entry & 127) {
+      o[3] = (int32_t)(entry & 127) - 1;
+      o[4] = 1 << g.part_log2;
+    }
+  }
+  return g.workgroups;
+}
+
 extern "C" tr_status tr_debug_philox(int64_t n, const uint32_t *ctr, const uint32_t *key,
                                      uint32_t *out, void *hip_stream) {
   if (n < 0 || (n > 0 && (!ctr || !key || !out))) return fail(TR_EINVAL, "tr_debug_philox: bad arguments");

@@ -68,8 +68,8 @@ constexpr int kQueueWords = (kQueueXcds + 1) * kQueueStride;
 // runs on XCD b mod 8), rotated: without the rotation a frame of 8 k chunks a
 // row gives each XCD the same columns in every row, and the XCDs of the middle
 // columns finish last.  Chunks are rotated by j, single tiles by a hash of j.
-__device__ __forceinline__ int64_t group_entry(uint32_t b, uint32_t whole, int32_t part_log2,
-                                               int32_t chunk_log2, int64_t n_tiles) {
+__host__ __device__ __forceinline__ int64_t group_entry(uint32_t b, uint32_t whole, int32_t part_log2,
+                                                        int32_t chunk_log2, int64_t n_tiles) {
   const uint32_t e = b / kQueueXcds;
   const uint32_t split = e < whole ? 0u : e - whole;
   const uint32_t i = e < whole ? e : whole + (split >> part_log2);
@@ -84,11 +84,11 @@ __device__ __forceinline__ int64_t group_entry(uint32_t b, uint32_t whole, int32
 // Tile t of a whole frame launched in chunks: bands of rows, each dealt column
 // by column, so that a chunk is a block of tiles (8 x 4 of 32, 16 x 8 of 128;
 // the last band has the rows that are left).
-__device__ __forceinline__ void block_tile(uint32_t t, uint32_t tiles_x, uint32_t tiles_y,
-                                           int32_t chunk_log2, int32_t &tx, int32_t &ty) {
+__host__ __device__ __forceinline__ void block_tile(uint32_t t, uint32_t tiles_x, uint32_t tiles_y,
+                                                    int32_t chunk_log2, int32_t &tx, int32_t &ty) {
   const uint32_t band = 1u << ((chunk_log2 + 1) >> 1);
   const uint32_t k = t / (band * tiles_x), r = t - k * band * tiles_x;
-  const uint32_t rows = min(band, tiles_y - k * band);
+  const uint32_t left = tiles_y - k * band, rows = left < band ? left : band;
   tx = (int32_t)(r / rows);
   ty = (int32_t)(k * band + r - (uint32_t)tx * rows);
 }
