@@ -476,11 +476,12 @@ constexpr int kRefill64 = 32;  // lanes at work below which idle ones take new r
 
 template <bool LAYERED, bool TRI>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
-void k_render_f64(const JobDev J, int64_t n_tiles, uint32_t first, uint32_t whole, int32_t part_log2, int32_t chunk_log2) {
+void k_render_f64(const JobDev J, int64_t n_tiles, uint32_t first, uint32_t whole, int32_t part_log2, int32_t chunk_log2,
+                  uint32_t turn) {
   __shared__ LdsF64 L;
   const SceneDev &S = J.sc;
   const int32_t lane = threadIdx.x;
-  const int64_t entry = group_entry(first + blockIdx.x, whole, part_log2, chunk_log2, n_tiles);
+  const int64_t entry = group_entry(first + blockIdx.x, whole, part_log2, chunk_log2, turn, n_tiles);
   if (entry < 0) return;
   const uint32_t tile = (uint32_t)(entry >> 7), tiles_x = ((uint32_t)J.W + 7u) / 8u;
   int32_t tx = (int32_t)(tile % tiles_x), ty = (int32_t)(tile / tiles_x);
@@ -678,17 +679,17 @@ hipError_t launch_render_plain_f64(const trd::JobDev &job, uint64_t *stats, hipS
     return hipGetLastError();
   }
   const int64_t tiles = (((int64_t)job.W + 7) / 8) * (((int64_t)job.H + 7) / 8);
-  const Groups g = split_groups(tiles, 1, true, true);
+  const Groups g = split_groups(tiles, 1, true, true, (int32_t)(((int64_t)job.W + 7) / 8));
   // (several launches where the workgroups are more than HIP takes in one: frames
   // of a few columns and 10^8 rows.  Each but the last a multiple of 8, for the XCDs.)
   constexpr int64_t kMost = kMaxWorkgroups / trd::kQueueXcds * trd::kQueueXcds;
   for (int64_t at = 0; at < g.workgroups; at += kMost) {
     const unsigned n = (unsigned)std::min(kMost, g.workgroups - at);
     const uint32_t first = (uint32_t)at;
-    if (lay && tri) k_render_f64<true, true><<<n, 64, 0, st>>>(job, tiles, first, g.whole, g.part_log2, g.chunk_log2);
-    else if (lay) k_render_f64<true, false><<<n, 64, 0, st>>>(job, tiles, first, g.whole, g.part_log2, g.chunk_log2);
-    else if (tri) k_render_f64<false, true><<<n, 64, 0, st>>>(job, tiles, first, g.whole, g.part_log2, g.chunk_log2);
-    else k_render_f64<false, false><<<n, 64, 0, st>>>(job, tiles, first, g.whole, g.part_log2, g.chunk_log2);
+    if (lay && tri) k_render_f64<true, true><<<n, 64, 0, st>>>(job, tiles, first, g.whole, g.part_log2, g.chunk_log2, g.turn);
+    else if (lay) k_render_f64<true, false><<<n, 64, 0, st>>>(job, tiles, first, g.whole, g.part_log2, g.chunk_log2, g.turn);
+    else if (tri) k_render_f64<false, true><<<n, 64, 0, st>>>(job, tiles, first, g.whole, g.part_log2, g.chunk_log2, g.turn);
+    else k_render_f64<false, false><<<n, 64, 0, st>>>(job, tiles, first, g.whole, g.part_log2, g.chunk_log2, g.turn);
   }
   return hipGetLastError();
 }

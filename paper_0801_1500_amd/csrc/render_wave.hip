@@ -526,6 +526,7 @@ struct WaveArgs {
   uint32_t whole;       // groups of 8 tiles that are entries as they are; the later tiles are split
   int32_t part_log2;    // entries of a split tile, log2
   int32_t chunk_log2;   // tiles dealt together to an XCD, log2: blocks of whole frames, or 0
+  uint32_t turn;        // see group_entry
 };
 
 __device__ __forceinline__ int32_t find_job(const TR_CONST JobDev *jobs, int32_t n, int64_t tile) {
@@ -573,7 +574,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BVH ? (BANKS
   int32_t cur_key = -1;   // scene loaded in this wave
   int32_t scene_job = 0;  // a job whose scene is the current one
   if (SPLIT) {
-    held_tile = group_entry(blockIdx.x, A.whole, A.part_log2, A.chunk_log2, A.n_tiles);
+    held_tile = group_entry(blockIdx.x, A.whole, A.part_log2, A.chunk_log2, A.turn, A.n_tiles);
     if (held_tile < 0) return;
     held_job = scene_job = uni(find_job((const TR_CONST JobDev *)A.jobs, A.n_jobs, held_tile >> 7));
   }
@@ -1612,6 +1613,7 @@ static hipError_t launch_t(const WaveLaunch &L, hipStream_t st) {
   a.whole = L.whole;
   a.part_log2 = L.part_log2;
   a.chunk_log2 = L.chunk_log2;
+  a.turn = L.turn;
   k_render_wave<BANKS, RES, CNT, TRANS, TRI, BVH><<<L.n_waves, 64, 0, st>>>(a);
   return hipGetLastError();
 }

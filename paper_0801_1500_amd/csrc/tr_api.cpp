@@ -1453,18 +1453,22 @@ static void set_entries(trh::WaveLaunch &L, const JobDev *jobs, int64_t total, c
   L.part_log2 = -1;
   L.whole = 0;
   L.chunk_log2 = 0;
+  L.turn = UINT32_MAX;
   L.n_waves = (int32_t)std::min((int64_t)num_cus() * t.waves_per_cu, total);
   if (t.banks != d.banks || t.waves_per_cu != d.waves_per_cu || t.stripe != d.stripe || L.stats) return;
   bool whole_frames = true, one_scene = true;
+  int32_t largest = 0;
   for (int32_t i = 0; i < L.n_jobs; ++i) {
+    if (jobs[i].tile_end > jobs[largest].tile_end) largest = i;
     whole_frames &= jobs[i].tile_begin == 0 && jobs[i].tile_end == (int64_t)jobs[i].tiles_x * jobs[i].tiles_y;
     one_scene &= jobs[i].scene_key == jobs[0].scene_key;
   }
-  const trh::Groups g = trh::split_groups(total, L.n_jobs, whole_frames, one_scene);
+  const trh::Groups g = trh::split_groups(total, L.n_jobs, whole_frames, one_scene, jobs[largest].tiles_x);
   if (g.workgroups > trh::kMaxWorkgroups) return;
   L.whole = g.whole;
   L.part_log2 = g.part_log2;
   L.chunk_log2 = g.chunk_log2;
+  L.turn = g.turn;
   L.n_waves = (int32_t)g.workgroups;
 }
 
@@ -2389,16 +2393,21 @@ extern "C" tr_status tr_autotune(const tr_scene *s, const tr_camera *c, const tr
 extern "C" int64_t tr_debug_entries(int32_t n_jobs, const int32_t *tiles_x, const int32_t *tiles_y,
                                     int32_t ranges, int64_t capacity, int32_t *out) {
   if (n_jobs < 1 || !tiles_x || !tiles_y || capacity < 0 || (!out && capacity > 0)) return -1;
-  int64_t total = 0;
+  int64_t total = 0, most = 0;
+  int32_t width = 0;
   for (int32_t k = 0; k < n_jobs; ++k) {
     if (tiles_x[k] < 1 || tiles_y[k] < 1) return -1;
+    if ((int64_t)tiles_x[k] * tiles_y[k] > most) {
+      most = (int64_t)tiles_x[k] * tiles_y[k];
+      width = tiles_x[k];
+    }
     total += (int64_t)tiles_x[k] * tiles_y[k];
   }
-  const trh::Groups g = trh::split_groups(total, n_jobs, !ranges, true);
+  const trh::Groups g = trh::split_groups(total, n_jobs, !ranges, true, width);
   if (g.workgroups > trh::kMaxWorkgroups) return -1;
   for (int64_t b = 0; b < g.workgroups && b < capacity; ++b) {
     int32_t *o = out + 5 * b;
-    const int64_t entry = trd::group_entry((uint32_t)b, g.whole, g.part_log2, g.chunk_log2, total);
+    const int64_t entry = trd::group_entry((uint32_t)b, g.whole, g.part_log2, g.chunk_log2, g.turn, total);
     int64_t t = entry >> 7;
     int32_t k = -1;
     if (entry >= 0)

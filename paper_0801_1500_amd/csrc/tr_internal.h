@@ -144,9 +144,11 @@ struct Groups {
   uint32_t whole;     // in groups of 8 tiles
   int32_t part_log2;
   int32_t chunk_log2;
+  uint32_t turn;
   int64_t workgroups;         // of 64 threads; may exceed kMaxWorkgroups
 };
-inline Groups split_groups(int64_t tiles, int32_t n_jobs, bool blocks, bool one_scene) {
+// (tiles_x: of the largest frame)
+inline Groups split_groups(int64_t tiles, int32_t n_jobs, bool blocks, bool one_scene, int32_t tiles_x) {
   const int64_t split = (int64_t)((n_jobs > 1 ? 20.0 : 60.0) * std::sqrt((double)tiles));
   Groups g;
   g.part_log2 = tiles <= 1024 ? 3 : 2;
@@ -154,6 +156,10 @@ inline Groups split_groups(int64_t tiles, int32_t n_jobs, bool blocks, bool one_
   const int64_t in = (int64_t)trd::kQueueXcds << g.chunk_log2;  // tiles in a group of chunks
   g.whole = tiles > 1024 && tiles > split ? (uint32_t)((tiles - split) / in) << g.chunk_log2 : 0u;
   const int64_t groups = (tiles + in - 1) / in << g.chunk_log2;
+  // groups of 8 blocks in a band of 4 rows; an even number comes back to the same
+  // rotations after 8 / gcd(8, number) bands
+  const uint32_t band = tiles_x % 16 || g.chunk_log2 != 3 ? 1u : (uint32_t)tiles_x / 16u;
+  g.turn = band % 2u ? UINT32_MAX : band * (band % 8u == 0u ? 1u : band % 4u == 0u ? 2u : 4u);
   g.workgroups = (g.whole + ((groups - g.whole) << g.part_log2)) * trd::kQueueXcds;
   return g;
 }
@@ -171,6 +177,7 @@ struct WaveLaunch {
   uint32_t whole;            // groups of 8 tiles that are entries as they are
   int32_t part_log2;         // entries of each later tile, log2
   int32_t chunk_log2;        // see Groups
+  uint32_t turn;
   int32_t n_waves;           // waves launched
   int32_t resolve;
   int32_t trans;             // some job composites transparent layers

@@ -46,6 +46,29 @@ def test_every_part_once(lib, sizes, ranges):
         assert (seen == 1).all()
 
 
+@pytest.mark.parametrize("jobs,ranges", [(1, False), (2, False), (4, True)])
+def test_dealing_is_even(lib, jobs, ranges):
+    """Workgroup b runs on XCD b mod 8, which deals its workgroups out in turn.
+    Frames whose rays lie in a disk (a pixel there costs what 17 others do): no
+    XCD, and no eighth of one, may have a quarter more than its fair part,
+    whatever the frames' width.  (An XCD had 1.5 times its part at rows of 64
+    tiles; of ranges, an eighth had up to four times at rows of 32 and 64.)"""
+    for w in list(range(8, 36)) + [48, 57, 64, 73, 96, 128]:
+        h = 1100
+        y, x = np.mgrid[0:h, 0:64 * w]
+        disk = (x - 35.2 * w) ** 2 + (y - 0.525 * h) ** 2 < (0.42 * min(h, 64 * w)) ** 2
+        cost = 64.0 + 16.0 * disk.reshape(h, w, 64).sum(2)
+        if ranges:  # the middle half of the tiles, as rows of a frame of their own
+            cost = cost[h // 4:h // 4 + h // 2]
+        e = entries(lib, [(w, len(cost))] * jobs, ranges)
+        b = np.flatnonzero(e[:, 0] >= 0)
+        _, tx, ty, _, parts = e[b].T
+        c = cost[ty, tx] / parts
+        for unit in (b % 8, b % 64):
+            load = np.bincount(unit, c)
+            assert load.max() <= 1.25 * load.mean(), (w, load.max() / load.mean())
+
+
 def renders_launch_as_many(model, tr):
     s = tr.Scene(scenegen.tiny_scene(seed=4))
     for sizes, fp64 in (([(130, 67)], False), ([(700, 431)], False), ([(700, 431), (65, 9), (2048, 300)], False),
