@@ -679,7 +679,7 @@ hipError_t launch_render_plain_f64(const trd::JobDev &job, uint64_t *stats, hipS
     return hipGetLastError();
   }
   const int64_t tiles = (((int64_t)job.W + 7) / 8) * (((int64_t)job.H + 7) / 8);
-  const Groups g = split_groups(tiles, 1, true, true, (int32_t)(((int64_t)job.W + 7) / 8));
+  const Groups g = split_groups(tiles, 1, true, (int32_t)(((int64_t)job.W + 7) / 8));
   // (several launches where the workgroups are more than HIP takes in one: frames
   // of a few columns and 10^8 rows.  Each but the last a multiple of 8, for the XCDs.)
   constexpr int64_t kMost = kMaxWorkgroups / trd::kQueueXcds * trd::kQueueXcds;

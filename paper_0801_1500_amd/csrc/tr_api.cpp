@@ -1456,14 +1456,13 @@ static void set_entries(trh::WaveLaunch &L, const JobDev *jobs, int64_t total, c
   L.turn = UINT32_MAX;
   L.n_waves = (int32_t)std::min((int64_t)num_cus() * t.waves_per_cu, total);
   if (t.banks != d.banks || t.waves_per_cu != d.waves_per_cu || t.stripe != d.stripe || L.stats) return;
-  bool whole_frames = true, one_scene = true;
+  bool whole_frames = true;
   int32_t largest = 0;
   for (int32_t i = 0; i < L.n_jobs; ++i) {
     if (jobs[i].tile_end > jobs[largest].tile_end) largest = i;
     whole_frames &= jobs[i].tile_begin == 0 && jobs[i].tile_end == (int64_t)jobs[i].tiles_x * jobs[i].tiles_y;
-    one_scene &= jobs[i].scene_key == jobs[0].scene_key;
   }
-  const trh::Groups g = trh::split_groups(total, L.n_jobs, whole_frames, one_scene, jobs[largest].tiles_x);
+  const trh::Groups g = trh::split_groups(total, L.n_jobs, whole_frames, jobs[largest].tiles_x);
   if (g.workgroups > trh::kMaxWorkgroups) return;
   L.whole = g.whole;
   L.part_log2 = g.part_log2;
@@ -2403,7 +2402,7 @@ extern "C" int64_t tr_debug_entries(int32_t n_jobs, const int32_t *tiles_x, cons
     }
     total += (int64_t)tiles_x[k] * tiles_y[k];
   }
-  const trh::Groups g = trh::split_groups(total, n_jobs, !ranges, true, width);
+  const trh::Groups g = trh::split_groups(total, n_jobs, !ranges, width);
   if (g.workgroups > trh::kMaxWorkgroups) return -1;
   for (int64_t b = 0; b < g.workgroups && b < capacity; ++b) {
     int32_t *o = out + 5 * b;

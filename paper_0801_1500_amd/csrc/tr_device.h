@@ -99,8 +99,8 @@ __host__ __device__ __forceinline__ int64_t group_entry(uint32_t b, uint32_t who
 }
 
 // Tile t of a whole frame launched in chunks: bands of rows, each dealt column
-// by column, so that a chunk is a block of tiles (8 x 4 of 32, 16 x 8 of 128;
-// the last band has the rows that are left).
+// by column, so that a chunk of 8 tiles is a block 2 wide and 4 high (the last
+// band has the rows that are left).
 __host__ __device__ __forceinline__ void block_tile(uint32_t t, uint32_t tiles_x, uint32_t tiles_y,
                                                     int32_t chunk_log2, int32_t &tx, int32_t &ty) {
   const uint32_t band = 1u << ((chunk_log2 + 1) >> 1);

@@ -125,18 +125,16 @@ hipError_t launch_render_plain_f64(const trd::JobDev &job, uint64_t *stats, hipS
 // Entries of a launch of one workgroup per entry over tiles of n_jobs frames
 // (trd::group_entry): the first 8 whole tiles as they are, each later one in
 // 2^part_log2 parts.  Whole frames (blocks) of more than 1,024 tiles are dealt
-// to the XCDs in blocks of tiles, so that an L2 serves rays that visit the same
-// cells: 8 tiles (2 x 4), and 128 (8 x 16) in launches of several frames of a
-// megapixel and more of one scene, which have blocks enough to even out what
-// they cost.
-// One frame of 26,318 objects, single tiles / 8 / 32 / 128: 640 x 480 256, 245,
-// 241, 286 us; 965 x 1137 717, 697, 700, 734; 1930 x 2274 2200, 2177, 2195,
-// 2213; 3860 x 4548 8160, 8080, 8266, 8120; 26,560 triangles at 1930 x 2274
-// 4011, 3950, 3922, 3863.  4 antialiasing passes of 965 x 1137 2520, 2407,
-// 2395, 2317; 8 frames of 1080p over 10^6 objects, whose cells are four times
-// the L2s, 31.2, 30.2, 29.8, 29.7 ms (512 tiles: 30.8); 6 requests of mixed
-// sizes and scenes 1905, 1888, 1882, 1931.  Ranges of a frame's tiles run in
-// row order: single tiles.
+// to the XCDs in blocks of 2 x 4 tiles, so that an L2 serves rays that visit
+// the same cells.  One frame of 26,318 objects, single tiles / blocks of 8: 640 x
+// 480 256, 245 us; 965 x 1137 717, 697; 1930 x 2274 2200, 2177; 3860 x 4548
+// 8160, 8080; 4 antialiasing passes of 965 x 1137 2520, 2407; 8 frames of 1080p
+// over 10^6 objects, whose cells are four times the L2s, 31.2, 30.2 ms.  Larger
+// blocks leave the XCDs unlike shares of a frame: 128 tiles (8 x 16) are 1 to 3%
+// faster than 8 where the frame's width suits them and up to 14% slower where it
+// does not, slower than persistent waves too (8 frames over 10^6 objects, waves /
+// 8 / 128: 1152 x 864 5930, 5600, 6390 us; 1280 x 1024 8010, 7720, 8260; 1920 x
+// 1080 8920, 8580, 8490).  Ranges of a frame's tiles run in row order: single tiles.
 // A launch has fewer than 2^32 threads (HIP's limit for a dimension of the
 // grid); callers compare the count, split tail and all.
 constexpr int64_t kMaxWorkgroups = (int64_t)UINT32_MAX / 64;
@@ -148,17 +146,17 @@ struct Groups {
   int64_t workgroups;         // of 64 threads; may exceed kMaxWorkgroups
 };
 // (tiles_x: of the largest frame)
-inline Groups split_groups(int64_t tiles, int32_t n_jobs, bool blocks, bool one_scene, int32_t tiles_x) {
+inline Groups split_groups(int64_t tiles, int32_t n_jobs, bool blocks, int32_t tiles_x) {
   const int64_t split = (int64_t)((n_jobs > 1 ? 20.0 : 60.0) * std::sqrt((double)tiles));
   Groups g;
   g.part_log2 = tiles <= 1024 ? 3 : 2;
-  g.chunk_log2 = !blocks || tiles <= 1024 ? 0 : (one_scene && n_jobs > 2 && tiles / n_jobs >= 16384 ? 7 : 3);
+  g.chunk_log2 = blocks && tiles > 1024 ? 3 : 0;
   const int64_t in = (int64_t)trd::kQueueXcds << g.chunk_log2;  // tiles in a group of chunks
   g.whole = tiles > 1024 && tiles > split ? (uint32_t)((tiles - split) / in) << g.chunk_log2 : 0u;
   const int64_t groups = (tiles + in - 1) / in << g.chunk_log2;
   // groups of 8 blocks in a band of 4 rows; an even number comes back to the same
   // rotations after 8 / gcd(8, number) bands
-  const uint32_t band = tiles_x % 16 || g.chunk_log2 != 3 ? 1u : (uint32_t)tiles_x / 16u;
+  const uint32_t band = tiles_x % 16 ? 1u : (uint32_t)tiles_x / 16u;
   g.turn = band % 2u ? UINT32_MAX : band * (band % 8u == 0u ? 1u : band % 4u == 0u ? 2u : 4u);
   g.workgroups = (g.whole + ((groups - g.whole) << g.part_log2)) * trd::kQueueXcds;
   return g;
