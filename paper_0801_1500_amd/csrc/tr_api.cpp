@@ -1443,10 +1443,55 @@ static int64_t set_queue(JobDev *jobs, int32_t n) {
 // 512 441 -> 271, 965 x 1137 903 -> 722, 1448 x 1448 1258 -> 1005, 3860 x
 // 4548 8.25 -> 8.09 ms; 8 views of 1080p of 10^6 objects 32.5 -> 31.2 ms.
 // Persistent waves take what asks for them: three banks, tunings that set the
-// waves per compute unit or the stripe, and launches with a stats buffer,
-// whose counters every wave adds to at its end (about 7 ns an atomic on one
-// line: 35 ns for each of tens of thousands of workgroups), and launches of more
-// workgroups than HIP takes (4,300 megapixels in 64 x 1 tiles).
+// waves per compute unit or the stripe, launches with a stats buffer, whose
+// counters every wave adds to at its end (about 7 ns an atomic on one line: 35
+// ns for each of tens of thousands of workgroups), and launches of more
+// workgroups than HIP takes (4,300 megapixels in 64 x 1 tiles).  And launches of
+// few rays (few_rays).
+//
+// A wave of one tile ends on its longest ray with most lanes idle, where a
+// persistent wave goes on with the next tile's pixels; it matters where a tile
+// has few rays and they differ (more objects than a pixel or ten), and where the
+// launch has so many tiles with hits that its own tail, about a tile's rays,
+// does not.  Few rays: at least 3,000 tiles covered by the scenes for each ray of
+// a hit pixel, and an object for every 7 covered pixels; or 15,000 tiles and an
+// object for every 50.  Ratio of the times, one workgroup per entry to persistent
+// waves, at 0, 4, 8, 16 and 32 AO samples (tiles per ray in parentheses): 965 x
+// 1137 of 10^6 objects 1.26 (4,800), 1.07 (2,070), 0.96, 0.84, 0.76; of 200,000
+// 1.24 (7,200), 1.13 (2,400), 1.00, 0.89, 0.81; 16 views 512 x 512 of 200,000 1.25
+// (13,700), 1.16, 1.10 (2,700), 1.02, 0.97; 64 views 256 x 256 of 26,318 1.15, 1.09,
+// 1.07 (4,900), 1.01 (2,800), 0.98; 4 views of 1080p of 10^6 0.98, 1.00, 0.97
+// (5,500), 0.95, 0.93; 3860 x 4548 of 10^6 1.00, 1.06 (32,000), 1.04 (20,000), 1.01,
+// 1.00, of 26,318 0.92 to 0.96.  Over 270 launches of 2,000 to 10^6 objects the rule
+// is 0.9% above the better of the two (one workgroup always: 4.7%).  Triangles,
+// layers and the BVH walk, whose persistent waves hold fewer in flight, always
+// take one workgroup per entry (1.09 at most, 64 x 256 x 256 of 28,840 triangles).
+static bool few_rays(const JobDev *jobs, int32_t n) {
+  double tiles = 0.0, rays = 0.0, objects = 0.0;  // covered; times rays per pixel, objects per pixel
+  for (int32_t i = 0; i < n; ++i) {
+    const JobDev &J = jobs[i];
+    if (J.sc.n_t > 0 || J.layers > 1) return false;
+    // pixels within the bounding sphere's outline, as if it were centred
+    const double px = (double)J.W * J.H, r2 = J.sc.rb2_32;
+    const double v[3] = {J.sc.org[0] - J.eye[0], J.sc.org[1] - J.eye[1], J.sc.org[2] - J.eye[2]};
+    const double d2 = dot3(v, v), ahead = dot3(v, J.f);
+    double covered = px;
+    if (d2 > r2) {
+      if (ahead < 0.0 && ahead * ahead > r2) continue;  // behind the eye
+      const double across = std::sqrt(r2 / (d2 - r2)) / J.th * J.H;
+      covered = std::min(across, (double)J.W) * std::min(across, (double)J.H) *
+                (across < std::max(J.W, J.H) ? 0.25 * M_PI : 1.0);
+    }
+    if (!(covered >= 1.0)) continue;
+    const double t = (double)(J.tile_end - J.tile_begin) * (covered / px);
+    tiles += t;
+    rays += t * (1 + J.n_lights + J.S);
+    objects += t * ((double)J.sc.n_s + J.sc.n_c) / covered;
+  }
+  return (objects >= 0.15 * tiles && tiles * tiles >= 3000.0 * rays && tiles > 0.0) ||
+         (objects >= 0.02 * tiles && tiles * tiles >= 15000.0 * rays && tiles > 0.0);
+}
+
 static void set_entries(trh::WaveLaunch &L, const JobDev *jobs, int64_t total, const tr_tune &t) {
   tr_tune d;
   default_tune(&d);
@@ -1455,7 +1500,9 @@ static void set_entries(trh::WaveLaunch &L, const JobDev *jobs, int64_t total, c
   L.chunk_log2 = 0;
   L.turn = UINT32_MAX;
   L.n_waves = (int32_t)std::min((int64_t)num_cus() * t.waves_per_cu, total);
-  if (t.banks != d.banks || t.waves_per_cu != d.waves_per_cu || t.stripe != d.stripe || L.stats) return;
+  if (t.banks != d.banks || t.waves_per_cu != d.waves_per_cu || t.stripe != d.stripe || L.stats ||
+      (!t.accel && few_rays(jobs, L.n_jobs)))
+    return;
   bool whole_frames = true;
   int32_t largest = 0;
   for (int32_t i = 0; i < L.n_jobs; ++i) {

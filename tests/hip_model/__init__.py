@@ -37,6 +37,7 @@ def load():
                    ("model_mallocs", C.c_long), ("model_staged_changed", C.c_long), ("model_pending", C.c_long)):
         getattr(model, f).restype = res
     model.model_capacity.argtypes = [C.c_int, C.c_size_t]
+    model.model_radius.argtypes = [C.c_double]
     model.model_capture.argtypes = [C.c_void_p, C.c_int]
     torch = sys.modules["torch"] = types.ModuleType("torch")  # (the binding loads it first)
     torch.cuda = types.SimpleNamespace(is_available=lambda: True,

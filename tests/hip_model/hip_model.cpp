@@ -54,6 +54,7 @@ thread_local struct { Dim3 g, b; size_t sh; void *st; } cfg;
 int hold;  // 1: the next copy is held, 2: one is
 std::condition_variable_any held;
 long staged_changed;
+double radius;
 
 void merge(Clock &a, const Clock &b) { for (auto &k : b) if (a[k.first] < k.second) a[k.first] = k.second; }
 bool covers(const Clock &a, int s, long id) { auto i = a.find(s); return i != a.end() && i->second >= id; }
@@ -93,6 +94,7 @@ API long model_bad_waits() { return bad_waits; }
 API long model_misuse() { return misuse; }
 API long model_frees() { return frees; }
 API long model_mallocs() { return mallocs; }
+API void model_radius(double r) { radius = r; }  // of the scenes built from now on, about the origin
 API void model_fail_sync(int on) { fail_sync = on; }
 API void model_fail_new(int after) { fail_new = after; }  // the one after so many; -1 none
 API int model_failed_new() { return fail_new < 0; }
@@ -248,6 +250,8 @@ API int hipLaunchKernel(const void *f, Dim3 g, Dim3 b, void **args, size_t, void
   ++launches;
   const std::string &n = names[f];
   log_.push_back(n + " " + std::to_string(g.x) + " " + std::to_string(b.x));
+  // (what the host reads of a grid build: no references, and the bounding radius)
+  if (n.find("k_cell_scan") != std::string::npos) std::memcpy(*(char **)args[8] + 8, &radius, 8);
   if (n.find("k_put_jobs") != std::string::npos) touch(*(uintptr_t *)args[1], s, id, true);
   if (n.find("k_render_wave") != std::string::npos) touch(*(uintptr_t *)args[0], s, id, false);
   return kOk;

@@ -99,6 +99,34 @@ def tables_under_capture(model, tr):
     assert model.model_races() == 0
 
 
+def few_rays(model, tr):
+    """Launches of few rays over many objects take persistent waves (two banks),
+    others one workgroup per entry (one bank), through every entry point."""
+    model.model_radius(10.0)  # (seen from 30 away: 0.74 of the height)
+    scenes = {n: tr.Scene(scenegen.tiny_scene(seed=4, n=n)) for n in (64, 20000, 200000)}
+    for n, jobs, w, h, ao, waves in (
+            (200000, 1, 965, 1137, 0, True), (200000, 1, 965, 1137, 16, False), (64, 1, 965, 1137, 0, False),
+            (200000, 64, 256, 256, 4, True), (64, 64, 256, 256, 4, False), (200000, 1, 128, 128, 0, False),
+            (200000, 1, 3860, 4548, 0, True), (64, 1, 3860, 4548, 0, False), (20000, 64, 256, 256, 0, True), (20000, 1, 965, 1137, 0, False)):
+        for entry in ("render", "batch", "noalloc", "graph"):
+            if (entry == "render" and jobs > 1) or (entry == "noalloc" and jobs > 16):
+                continue
+            job = list(_job(tr, scenes[n], w, h))
+            job[2].ao_samples = ao
+            assert _render(tr, entry, [tuple(job)] * jobs) == 0
+            name, grid, _ = hip_model.launches(model)[-1]
+            assert ("k_render_waveILi2E" in name) == waves, (n, jobs, w, h, ao, entry, name)
+    away = list(_job(tr, scenes[200000], 965, 1137))
+    away[2].ao_samples = 0
+    away[1].lookat[2] = 60.0
+    assert _render(tr, "render", [tuple(away)]) == 0  # (nothing to be seen)
+    assert "k_render_waveILi1E" in hip_model.launches(model)[-1][0]
+
+
+def test_few_rays():
+    hip_model.run("test_host_launch", "few_rays")
+
+
 @pytest.mark.parametrize("test", ["tables_per_thread_stream", "tables_under_capture"])
 def test_job_tables(test):
     hip_model.run("test_host_launch", test)
