@@ -6,7 +6,7 @@
 // Two kernels give the same frames: k_render_f64, which queues the rays of a
 // tile's hits, and k_render_plain_f64, one thread per pixel over a plain
 // 3D-DDA, whose traversal counts are those of the method's definition (launches
-// with a stats buffer).
+// with a stats buffer, and frames with little to trace: see plain_is_faster).
 //
 // Compiled with -ffp-contract=off and written in the same expression order
 // as the definition of the method (camera, intersections, normals,
@@ -158,14 +158,16 @@ __device__ __forceinline__ void normal_f64(const SceneDev &S, int32_t k, const d
   }
 }
 
-// The counting kernel.  Variants: layered compositing and triangles are compiled
-// in only for jobs that need them (either costs registers, and so occupancy,
-// in the others).
-template <bool LAYERED, bool TRI>
+// One thread per pixel.  Variants: counting, layered compositing and triangles are
+// compiled in only for jobs that need them (each costs registers, and so
+// occupancy, in the others).
+template <bool STATS, bool LAYERED, bool TRI>
 __global__ __launch_bounds__(256) void k_render_plain_f64(const JobDev J, uint64_t *stats) {
   __shared__ uint32_t red[TR_STAT_COUNT];
-  if (threadIdx.x < TR_STAT_COUNT) red[threadIdx.x] = 0;
-  __syncthreads();
+  if (STATS) {
+    if (threadIdx.x < TR_STAT_COUNT) red[threadIdx.x] = 0;
+    __syncthreads();
+  }
   const int32_t i = blockIdx.x * 16 + (threadIdx.x & 15);
   const int32_t j = blockIdx.y * 16 + (threadIdx.x >> 4);
   Cnt c{0, 0, 0, 0, 0, 0, 0, 0};
@@ -283,22 +285,26 @@ __global__ __launch_bounds__(256) void k_render_plain_f64(const JobDev J, uint64
     if (J.hit_id) J.hit_id[pid] = hit ? k0 : -1;
     if (J.ao_mask) J.ao_mask[pid] = amask;
     if (J.light_mask) J.light_mask[pid] = (uint8_t)lmask;
-    atomicAdd(&red[TR_STAT_PIXELS], 1u);
-    atomicAdd(&red[TR_STAT_HIT_PIXELS], n_hit);
-    atomicAdd(&red[TR_STAT_AO_RAYS], n_ao);
-    atomicAdd(&red[TR_STAT_SHADOW_RAYS], n_sh);
-    atomicAdd(&red[TR_STAT_RAYS_TRACED], c.rays);
-    atomicAdd(&red[TR_STAT_CELLS], c.cells);
-    atomicAdd(&red[TR_STAT_SPH_TESTS], c.st);
-    atomicAdd(&red[TR_STAT_SPH_HITS], c.sh);
-    atomicAdd(&red[TR_STAT_CYL_TESTS], c.ct);
-    atomicAdd(&red[TR_STAT_CYL_HITS], c.ch);
-    atomicAdd(&red[TR_STAT_TRI_TESTS], c.tt);
-    atomicAdd(&red[TR_STAT_TRI_HITS], c.th);
+    if (STATS) {
+      atomicAdd(&red[TR_STAT_PIXELS], 1u);
+      atomicAdd(&red[TR_STAT_HIT_PIXELS], n_hit);
+      atomicAdd(&red[TR_STAT_AO_RAYS], n_ao);
+      atomicAdd(&red[TR_STAT_SHADOW_RAYS], n_sh);
+      atomicAdd(&red[TR_STAT_RAYS_TRACED], c.rays);
+      atomicAdd(&red[TR_STAT_CELLS], c.cells);
+      atomicAdd(&red[TR_STAT_SPH_TESTS], c.st);
+      atomicAdd(&red[TR_STAT_SPH_HITS], c.sh);
+      atomicAdd(&red[TR_STAT_CYL_TESTS], c.ct);
+      atomicAdd(&red[TR_STAT_CYL_HITS], c.ch);
+      atomicAdd(&red[TR_STAT_TRI_TESTS], c.tt);
+      atomicAdd(&red[TR_STAT_TRI_HITS], c.th);
+    }
   }
-  __syncthreads();
-  if (threadIdx.x < TR_STAT_COUNT && red[threadIdx.x])
-    atomicAdd((unsigned long long *)&stats[threadIdx.x], (unsigned long long)red[threadIdx.x]);
+  if (STATS) {
+    __syncthreads();
+    if (threadIdx.x < TR_STAT_COUNT && red[threadIdx.x])
+      atomicAdd((unsigned long long *)&stats[threadIdx.x], (unsigned long long)red[threadIdx.x]);
+  }
 }
 
 // ------------------------------------------------ the queued FP64 renderer
@@ -668,18 +674,46 @@ void k_render_f64(const JobDev J, int64_t n_tiles, uint32_t first, uint32_t whol
 
 namespace trh {
 
+// Whether one thread per pixel is the faster kernel.  The queued kernel costs
+// 2.4 ns for each workgroup (a wave a tile, 1.2 to 8 of them; 1080p 154 us for
+// a frame of background, where a thread per pixel takes 31), and its rays 2 to 9
+// times less the more objects there are; a thread traces its pixel's rays one
+// after the other, so a small frame takes as long as its slowest pixel.
+// Modelled on 128 x 128 to 3860 x 4548, 0 to 16 AO samples, 1 to 10^6 objects,
+// whole views, far ones and background; measured, us, queued / thread per pixel:
+// one sphere at 1080p, 0, 4 and 16 samples 163 / 47, 210 / 98, 326 / 245, at 128 x
+// 128 22 / 18, 23 / 28, 28 / 61; 64 spheres at 965 x 1137 178 / 78, 298 / 254, 559 /
+// 774; 26,318 objects at 965 x 1137 408 / 400, 687 / 1359, 1355 / 4230.  Over those
+// launches the choice is within a tenth of the better kernel, but for some frames of
+// 64 spheres (3860 x 4548 at 4 samples 2910 / 2430, 320 x 240 at none 52 / 40).
+static bool plain_is_faster(const trd::JobDev &job, int64_t workgroups) {
+  if (job.layers > 1) return false;
+  const double n = std::max(1.0, (double)job.sc.n_s + job.sc.n_c + job.sc.n_t);
+  const double rays = 1 + job.n_lights + job.S, traced = rays * covered_pixels(job);
+  // ns; the slowest pixel's beyond what a queued wave waits for too
+  const double slowest = traced > 0.0 ? 2500.0 * rays * std::pow(n, 0.36) : 0.0;
+  const double plain = 0.015 * ((double)job.W * job.H) + 0.0147 * std::pow(n, 0.28) * traced;
+  const double queued = 2.4 * (double)workgroups + 0.015 * std::pow(n, 0.19) * traced;
+  return std::max(slowest, plain) < queued;
+}
+
+template <bool STATS, bool LAYERED>
+static void launch_plain(const trd::JobDev &job, uint64_t *stats, hipStream_t st) {
+  const dim3 grid((unsigned)(((int64_t)job.W + 15) / 16), (unsigned)(((int64_t)job.H + 15) / 16));
+  if (job.sc.n_t > 0) k_render_plain_f64<STATS, LAYERED, true><<<grid, 256, 0, st>>>(job, stats);
+  else k_render_plain_f64<STATS, LAYERED, false><<<grid, 256, 0, st>>>(job, stats);
+}
+
 hipError_t launch_render_plain_f64(const trd::JobDev &job, uint64_t *stats, hipStream_t st) {
   const bool lay = job.layers > 1, tri = job.sc.n_t > 0;
-  if (stats) {  // the counted walk: a plain 3D-DDA, one thread per pixel
-    const dim3 grid((unsigned)((job.W + 15) / 16), (unsigned)((job.H + 15) / 16));
-    if (lay && tri) k_render_plain_f64<true, true><<<grid, 256, 0, st>>>(job, stats);
-    else if (lay) k_render_plain_f64<true, false><<<grid, 256, 0, st>>>(job, stats);
-    else if (tri) k_render_plain_f64<false, true><<<grid, 256, 0, st>>>(job, stats);
-    else k_render_plain_f64<false, false><<<grid, 256, 0, st>>>(job, stats);
-    return hipGetLastError();
-  }
   const int64_t tiles = (((int64_t)job.W + 7) / 8) * (((int64_t)job.H + 7) / 8);
   const Groups g = split_groups(tiles, 1, true, (int32_t)(((int64_t)job.W + 7) / 8));
+  if (stats || plain_is_faster(job, g.workgroups)) {
+    if (!stats) launch_plain<false, false>(job, nullptr, st);
+    else if (lay) launch_plain<true, true>(job, stats, st);
+    else launch_plain<true, false>(job, stats, st);
+    return hipGetLastError();
+  }
   // (several launches where the workgroups are more than HIP takes in one: frames
   // of a few columns and 10^8 rows.  Each but the last a multiple of 8, for the XCDs.)
   constexpr int64_t kMost = kMaxWorkgroups / trd::kQueueXcds * trd::kQueueXcds;

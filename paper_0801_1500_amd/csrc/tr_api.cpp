@@ -1471,19 +1471,9 @@ static bool few_rays(const JobDev *jobs, int32_t n) {
   for (int32_t i = 0; i < n; ++i) {
     const JobDev &J = jobs[i];
     if (J.sc.n_t > 0 || J.layers > 1) return false;
-    // pixels within the bounding sphere's outline, as if it were centred
-    const double px = (double)J.W * J.H, r2 = J.sc.rb2_32;
-    const double v[3] = {J.sc.org[0] - J.eye[0], J.sc.org[1] - J.eye[1], J.sc.org[2] - J.eye[2]};
-    const double d2 = dot3(v, v), ahead = dot3(v, J.f);
-    double covered = px;
-    if (d2 > r2) {
-      if (ahead < 0.0 && ahead * ahead > r2) continue;  // behind the eye
-      const double across = std::sqrt(r2 / (d2 - r2)) / J.th * J.H;
-      covered = std::min(across, (double)J.W) * std::min(across, (double)J.H) *
-                (across < std::max(J.W, J.H) ? 0.25 * M_PI : 1.0);
-    }
+    const double covered = trh::covered_pixels(J);
     if (!(covered >= 1.0)) continue;
-    const double t = (double)(J.tile_end - J.tile_begin) * (covered / px);
+    const double t = (double)(J.tile_end - J.tile_begin) * (covered / ((double)J.W * J.H));
     tiles += t;
     rays += t * (1 + J.n_lights + J.S);
     objects += t * ((double)J.sc.n_s + J.sc.n_c) / covered;

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <string>
 
@@ -120,6 +121,23 @@ hipError_t launch_aa_mean(float *rgb, const float *planes, int32_t n_planes, int
                           hipStream_t st);
 
 // ---- render launchers ----
+// Pixels of the job's frame that its scene may cover: the outline of the
+// bounding sphere, as if it were centred (all of them from inside, none with
+// the sphere behind the eye).
+inline double covered_pixels(const trd::JobDev &J) {
+  const double px = (double)J.W * J.H, r2 = J.sc.rb2_32;
+  double d2 = 0.0, ahead = 0.0;
+  for (int a = 0; a < 3; ++a) {
+    const double v = J.sc.org[a] - J.eye[a];
+    d2 += v * v;
+    ahead += v * J.f[a];
+  }
+  if (!(d2 > r2)) return px;
+  if (ahead < 0.0 && ahead * ahead > r2) return 0.0;
+  const double across = std::sqrt(r2 / (d2 - r2)) / J.th * J.H;
+  return std::min(across, (double)J.W) * std::min(across, (double)J.H) *
+         (across < std::max(J.W, J.H) ? 0.25 * M_PI : 1.0);
+}
 hipError_t launch_render_plain_f64(const trd::JobDev &job, uint64_t *stats, hipStream_t st);
 
 // Entries of a launch of one workgroup per entry over tiles of n_jobs frames

@@ -54,10 +54,13 @@ def large_fp32(model, tr):
 def large_fp64(model, tr):
     """Narrow FP64 frames of 2^26 tiles and more: all entries in launches that
     the runtime takes."""
-    s = tr.Scene(scenegen.tiny_scene(seed=4))
+    model.model_radius(10.0)
+    s = tr.Scene(scenegen.tiny_scene(seed=4, n=20000))  # (objects enough for the queued kernel)
     for height in (8 * 5000, 8 * (LIMIT - 1), 8 * LIMIT, 2 ** 31 - 2):
         before = len(hip_model.launches(model))
-        assert _render(tr, "render", [_job(tr, s, 1, height, "fp64")]) == 0, (height, tr.lib().tr_last_error())
+        job = _job(tr, s, 1, height, "fp64")
+        job[2].ao_samples = 16
+        assert _render(tr, "render", [job]) == 0, (height, tr.lib().tr_last_error())
         grids = [g for n, g, b in hip_model.launches(model)[before:] if "k_render_f64" in n]
         tiles = (height + 7) // 8
         split = int(60.0 * tiles ** 0.5)
@@ -123,8 +126,29 @@ def few_rays(model, tr):
     assert "k_render_waveILi1E" in hip_model.launches(model)[-1][0]
 
 
-def test_few_rays():
-    hip_model.run("test_host_launch", "few_rays")
+def fp64_kernels(model, tr):
+    """FP64 frames with little to trace go to one thread per pixel, others to
+    the queued kernel."""
+    model.model_radius(10.0)
+    scenes = {n: tr.Scene(scenegen.tiny_scene(seed=4, n=n)) for n in (1, 64, 20000)}
+    for n, w, h, ao, away, plain in (
+            (1, 1920, 1080, 0, False, True), (1, 1920, 1080, 16, False, True), (1, 128, 128, 16, False, False),
+            (64, 965, 1137, 0, False, True), (64, 965, 1137, 16, False, False), (64, 128, 128, 8, False, False),
+            (20000, 965, 1137, 0, False, False), (20000, 965, 1137, 16, False, False),
+            (20000, 965, 1137, 16, True, True)):
+        job = _job(tr, scenes[n], w, h, "fp64")
+        job[2].ao_samples = ao
+        if away:
+            job[1].lookat[2] = 60.0
+        for entry in ("render", "batch", "noalloc"):
+            assert _render(tr, entry, [job]) == 0
+            name = hip_model.launches(model)[-1][0]
+            assert ("k_render_plain_f64ILb0ELb0E" in name) == plain, (n, w, h, ao, away, entry, name)
+
+
+@pytest.mark.parametrize("test", ["few_rays", "fp64_kernels"])
+def test_kernel_choice(test):
+    hip_model.run("test_host_launch", test)
 
 
 @pytest.mark.parametrize("test", ["tables_per_thread_stream", "tables_under_capture"])
