@@ -48,8 +48,8 @@ typedef enum {
 
 /* Arithmetic of the render.  The paper's renderer computes in double
  * precision throughout (Sec. 2).  TR_PREC_FP64 is that plain FP64 path on
- * the GPU (one thread per pixel).  TR_PREC_FP32 intersects and shades in
- * FP32 in the persistent-wavefront kernel; TR_PREC_FP32_RESOLVE adds an
+ * the GPU (every step in FP64).  TR_PREC_FP32 intersects and shades in
+ * FP32 in the wavefront kernel; TR_PREC_FP32_RESOLVE adds an
  * FP64 re-solve of near-grazing sphere/cylinder tests (the default). */
 typedef enum {
   TR_PREC_FP64 = 0,
@@ -219,7 +219,8 @@ enum {
   TR_STAT_COUNT
 };
 
-/* Launch shape of the persistent-wavefront kernel.  Any valid choice of the
+/* Launch shape of the wavefront kernel: one wave per tile or part of a tile, or
+ * persistent waves that draw tiles from a queue.  Any valid choice of the
  * shape fields gives bit-identical frames; only speed changes.  accel picks
  * the acceleration structure instead (see there).  Zero fields take
  * defaults. */
@@ -227,9 +228,10 @@ typedef struct {
   int32_t tile_w;            /* tile width in pixels: 4, 8, 16, 32 or 64; tiles hold 64
                                 pixels (default 64: one row segment per tile) */
   int32_t banks;             /* pixel banks (tiles in flight) per wave: 2 or 3 (queue depth) */
-  int32_t waves_per_cu;      /* persistent waves launched per compute unit, 1..32; with
+  int32_t waves_per_cu;      /* persistent waves launched per compute unit, 1..32.  With
                                 the default here and in banks and stripe, and no stats
-                                buffer, one wave per tile or part of a tile instead */
+                                buffer: one wave per tile or part of a tile, unless the
+                                launch has few rays for its tiles and objects */
   int32_t refill_below;      /* refill when fewer than this many lanes are busy, 1..64 */
   int32_t count_ops;         /* 1 = also fill the traversal counters of tr_frame.stats */
   int32_t accel;             /* 0 = walk the uniform grid; 1 = walk the scene's
@@ -378,8 +380,8 @@ tr_status tr_render(const tr_scene *scene, const tr_camera *cam, const tr_params
 tr_status tr_render_tuned(const tr_scene *scene, const tr_camera *cam, const tr_params *params,
                           const tr_frame *frame, const tr_tune *tune, void *hip_stream);
 
-/* Render n frames in ONE persistent launch whose tile queue spans all n
- * jobs (scenes may differ; job i uses scenes[i], cams[i], params[i],
+/* Render n frames in ONE launch whose tiles are those of all n jobs
+ * (scenes may differ; job i uses scenes[i], cams[i], params[i],
  * frames[i]).  The FP32 jobs share one launch: they must all use the first
  * FP32 job's precision and its stats buffer (which may be NULL), and that
  * job picks the launch shape.  TR_PREC_FP64 jobs are rendered one launch
@@ -469,8 +471,8 @@ int64_t tr_tga_max_bytes(int32_t width, int32_t height);
 
 /* ------------------------------------------------ graphs (batched views) */
 
-/* A captured, replayable batch render: the tile-counter reset and the
- * persistent launch recorded once into a hipGraph.  Cameras and parameters
+/* A captured, replayable batch render: the launch (and, for persistent waves,
+ * the reset of their tile counter) recorded once into a hipGraph.  Cameras and parameters
  * live in a device job table, so tr_graph_update changes views without
  * re-capturing.  The jobs follow tr_render_batch's rules, and in addition
  * need an FP32 precision, aa_samples <= 1 and max_layers <= 1 (else
