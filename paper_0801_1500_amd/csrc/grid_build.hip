@@ -900,7 +900,10 @@ __device__ __forceinline__ void node_box(const trh::BuildArgs &a, const uint32_t
 // not a launch.  26,318 leaves: all levels in 16 + 20 us, the whole build
 // 308 -> 129 us (with the depths and the sort in fewer launches, above).
 constexpr int kBvhChunk = 512;
-constexpr int64_t kBvhSmall = 131072;  // a node's index fits the list's 18 bits
+// Up to here: a node's index fits the list's 18 bits, and the last workgroup's share
+// has grown to what the levels' launches cost (a build in chunks / by levels, with
+// its wait: 8,000 leaves 113 / 225 us, 26,000 127 / 232, 65,000 182 / 250, 131,072 268 / 260).
+constexpr int64_t kBvhSmall = 131072;
 
 __global__ __launch_bounds__(kBvhChunk) void k_bvh_chunks(const trh::BuildArgs a, const uint32_t *vals,
                                                           int64_t m, const int32_t *dep,
