@@ -1463,23 +1463,36 @@ static int64_t set_queue(JobDev *jobs, int32_t n) {
 // 1.07 (4,900), 1.01 (2,800), 0.98; 4 views of 1080p of 10^6 0.98, 1.00, 0.97
 // (5,500), 0.95, 0.93; 3860 x 4548 of 10^6 1.00, 1.06 (32,000), 1.04 (20,000), 1.01,
 // 1.00, of 26,318 0.92 to 0.96.  Over 270 launches of 2,000 to 10^6 objects the rule
-// is 0.9% above the better of the two (one workgroup always: 4.7%).  Triangles,
-// layers and the BVH walk, whose persistent waves hold fewer in flight, always
-// take one workgroup per entry (1.09 at most, 64 x 256 x 256 of 28,840 triangles).
+// is 0.9% above the better of the two (one workgroup always: 4.7%).
+// With triangles the lines are 2,000 tiles and an object for every 4.5 pixels
+// (965 x 1137 of 200,000 triangles at 0, 4 and 8 samples 1.32, 1.27, 1.09; 64 views
+// 256 x 256 of 26,560 at 0, 4 and 16 1.20, 1.11, 0.96; 16 views 512 x 512, 0.17 a pixel,
+// 1.05, 0.99, 0.87; 0.9% against 6% over 120 launches).  With layers, whose persistent
+// waves are 3 a SIMD for 6, they are 5,000 and 1.5 objects a pixel, or 12,000 and one
+// for every 2 (200,000 objects, 64 views 256 x 256 at 0, 2, 4 and 8 samples 1.18, 1.04,
+// 1.00, 0.91, 16 views 512 x 512, 1.2 a pixel, 1.08, 0.92, 0.87; 0.4% against 1.6% over
+// 80, the worst 965 x 1137 at no sample, 0.26 a pixel, 1.20, where four views of 1080p
+// are 0.96).  The BVH walk always takes one workgroup per entry.
 static bool few_rays(const JobDev *jobs, int32_t n) {
   double tiles = 0.0, rays = 0.0, objects = 0.0;  // covered; times rays per pixel, objects per pixel
+  bool tri = false, layers = false;
   for (int32_t i = 0; i < n; ++i) {
     const JobDev &J = jobs[i];
-    if (J.sc.n_t > 0 || J.layers > 1) return false;
+    tri |= J.sc.n_t > 0;
+    layers |= J.layers > 1;
     const double covered = trh::covered_pixels(J);
     if (!(covered >= 1.0)) continue;
     const double t = (double)(J.tile_end - J.tile_begin) * (covered / ((double)J.W * J.H));
     tiles += t;
     rays += t * (1 + J.n_lights + J.S);
-    objects += t * ((double)J.sc.n_s + J.sc.n_c) / covered;
+    objects += t * ((double)J.sc.n_s + J.sc.n_c + J.sc.n_t) / covered;
   }
-  return (objects >= 0.15 * tiles && tiles * tiles >= 3000.0 * rays && tiles > 0.0) ||
-         (objects >= 0.02 * tiles && tiles * tiles >= 15000.0 * rays && tiles > 0.0);
+  const auto at_least = [&](double per_ray, double per_pixel) {
+    return tiles > 0.0 && tiles * tiles >= per_ray * rays && objects >= per_pixel * tiles;
+  };
+  if (layers) return at_least(5000.0, 1.5) || at_least(12000.0, 0.5);
+  if (tri) return at_least(2000.0, 0.22);
+  return at_least(3000.0, 0.15) || at_least(15000.0, 0.02);
 }
 
 static void set_entries(trh::WaveLaunch &L, const JobDev *jobs, int64_t total, const tr_tune &t) {

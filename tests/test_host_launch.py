@@ -5,6 +5,7 @@ stream, under capture and with tables that grow."""
 import ctypes as C
 import threading
 
+import numpy as np
 import pytest
 
 import hip_model
@@ -119,6 +120,19 @@ def few_rays(model, tr):
             assert _render(tr, entry, [tuple(job)] * jobs) == 0
             name, grid, _ = hip_model.launches(model)[-1]
             assert ("k_render_waveILi2E" in name) == waves, (n, jobs, w, h, ao, entry, name)
+    glass = scenegen.tiny_scene(seed=4, n=200000)
+    glass.sph_opacity = np.full(200000, 0.5, np.float32)
+    corners = np.random.default_rng(1).normal(size=(200000, 3, 3))
+    kinds = {"layers": tr.Scene(glass), "triangles": tr.Scene(scenegen.with_triangles(scenegen.tiny_scene(n=0), corners))}
+    for kind, jobs, w, h, ao, waves in (
+            ("layers", 64, 256, 256, 0, True), ("layers", 64, 256, 256, 8, False), ("layers", 1, 965, 1137, 0, False),
+            ("triangles", 64, 256, 256, 8, True), ("triangles", 64, 256, 256, 32, False),
+            ("triangles", 1, 965, 1137, 0, True), ("triangles", 1, 965, 1137, 16, False)):
+        job = list(_job(tr, kinds[kind], w, h))
+        job[2].ao_samples, job[2].max_layers = ao, 4
+        assert _render(tr, "batch", [tuple(job)] * jobs) == 0
+        name = hip_model.launches(model)[-1][0]
+        assert ("k_render_waveILi2E" in name) == waves, (kind, jobs, w, h, ao, name)
     away = list(_job(tr, scenes[200000], 965, 1137))
     away[2].ao_samples = 0
     away[1].lookat[2] = 60.0
