@@ -685,11 +685,12 @@ namespace trh {
 // 128 22 / 18, 23 / 28, 28 / 61; 64 spheres at 965 x 1137 178 / 78, 298 / 254, 559 /
 // 774; 26,318 objects at 965 x 1137 408 / 400, 687 / 1359, 1355 / 4230.  Over those
 // launches the choice is within a tenth of the better kernel, but for some frames of
-// 64 spheres (3860 x 4548 at 4 samples 2910 / 2430, 320 x 240 at none 52 / 40).
+// 64 spheres (3860 x 4548 at 4 samples 2910 / 2430, 320 x 240 at none 52 / 40).  With
+// layers a pixel's rays are taken twice (64 spheres at opacity 0.5, up to 4 layers, no
+// AO, 640 x 480 138 / 85, 1080p 251 / 177).
 static bool plain_is_faster(const trd::JobDev &job, int64_t workgroups) {
-  if (job.layers > 1) return false;
   const double n = std::max(1.0, (double)job.sc.n_s + job.sc.n_c + job.sc.n_t);
-  const double rays = 1 + job.n_lights + job.S, traced = rays * covered_pixels(job);
+  const double rays = (1 + job.n_lights + job.S) * (job.layers > 1 ? 2 : 1), traced = rays * covered_pixels(job);
   // ns; the slowest pixel's beyond what a queued wave waits for too
   const double slowest = traced > 0.0 ? 2500.0 * rays * std::pow(n, 0.36) : 0.0;
   const double plain = 0.015 * ((double)job.W * job.H) + 0.0147 * std::pow(n, 0.28) * traced;
@@ -709,7 +710,8 @@ hipError_t launch_render_plain_f64(const trd::JobDev &job, uint64_t *stats, hipS
   const int64_t tiles = (((int64_t)job.W + 7) / 8) * (((int64_t)job.H + 7) / 8);
   const Groups g = split_groups(tiles, 1, true, (int32_t)(((int64_t)job.W + 7) / 8));
   if (stats || plain_is_faster(job, g.workgroups)) {
-    if (!stats) launch_plain<false, false>(job, nullptr, st);
+    if (!stats && lay) launch_plain<false, true>(job, nullptr, st);
+    else if (!stats) launch_plain<false, false>(job, nullptr, st);
     else if (lay) launch_plain<true, true>(job, stats, st);
     else launch_plain<true, false>(job, stats, st);
     return hipGetLastError();

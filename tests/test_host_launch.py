@@ -158,6 +158,15 @@ def fp64_kernels(model, tr):
             assert _render(tr, entry, [job]) == 0
             name = hip_model.launches(model)[-1][0]
             assert ("k_render_plain_f64ILb0ELb0E" in name) == plain, (n, w, h, ao, away, entry, name)
+    glass = scenegen.tiny_scene(seed=4)
+    glass.sph_opacity = np.full(64, 0.5, np.float32)
+    for ao, plain in ((0, True), (16, False)):
+        job = _job(tr, tr.Scene(glass), 965, 1137, "fp64")
+        job[2].ao_samples, job[2].max_layers = ao, 4
+        for entry in ("render", "batch", "noalloc"):
+            assert _render(tr, entry, [job]) == 0
+            name = hip_model.launches(model)[-1][0]
+            assert ("k_render_plain_f64ILb0ELb1E" in name) == plain, (ao, entry, name)
 
 
 @pytest.mark.parametrize("test", ["few_rays", "fp64_kernels"])
