@@ -1334,30 +1334,16 @@ static tr_tune pick_tune(const tr_scene *s, const tr_camera *c, const tr_params 
 // colours into plane a - 1 of a per-stream workspace.  After the render,
 // one pass per frame folds the planes into the caller's rgb, summing in
 // sample order (deterministic), and divides by A.
+// One thread at a time uses a workspace, from its sample jobs to its folds, so
+// no other grows it in between; on hipStreamPerThread, which is another stream
+// in every thread, the work waits on the device for the last that used it.
 struct AAWork {
+  std::mutex mu;
   float *buf = nullptr;
-  int64_t cap = 0;  // floats
+  int64_t cap = 0;            // floats
+  hipEvent_t done = nullptr;  // hipStreamPerThread: the last folds
 };
 static std::map<std::pair<int, hipStream_t>, AAWork> g_aa_work;
-
-static tr_status aa_workspace(hipStream_t st, int64_t n_floats, float **out) {
-  int dev = 0;
-  (void)hipGetDevice(&dev);
-  std::lock_guard<std::mutex> lk(g_mu);
-  AAWork &w = g_aa_work[{dev, st}];
-  if (w.cap < n_floats) {
-    if (w.buf) {  // earlier work on this stream may still read the old planes
-      HIP_TRY(hipStreamSynchronize(st));
-      HIP_TRY(hipFree(w.buf));
-      w.buf = nullptr;
-      w.cap = 0;
-    }
-    HIP_TRY(device_malloc((void **)&w.buf, (size_t)n_floats * sizeof(float)));
-    w.cap = n_floats;
-  }
-  *out = w.buf;
-  return TR_OK;
-}
 
 struct AAMean {
   float *rgb;
@@ -1366,15 +1352,53 @@ struct AAMean {
   int64_t n;  // floats per plane (W * H * 3)
 };
 
+struct AAFolds {
+  std::vector<AAMean> means;
+  std::unique_lock<std::mutex> lk;  // the workspace's
+  hipEvent_t done = nullptr;
+  ~AAFolds() {  // (also after a failed launch: some samples may be written)
+    if (done) (void)hipEventRecord(done, hipStreamPerThread);
+  }
+};
+
+static tr_status aa_workspace(hipStream_t st, int64_t n_floats, AAFolds &folds, float **out) {
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  AAWork *work = nullptr;
+  {
+    std::lock_guard<std::mutex> lk(g_mu);
+    work = &g_aa_work[{dev, st}];  // (entries stay where they are)
+  }
+  AAWork &w = *work;
+  folds.lk = std::unique_lock<std::mutex>(w.mu);
+  if (w.cap < n_floats) {
+    if (w.buf) {  // earlier work may still read the old planes
+      HIP_TRY(hipStreamSynchronize(st));
+      HIP_TRY(hipFree(w.buf));  // (waits for the device)
+      w.buf = nullptr;
+      w.cap = 0;
+    }
+    HIP_TRY(device_malloc((void **)&w.buf, (size_t)n_floats * sizeof(float)));
+    w.cap = n_floats;
+  }
+  if (st == hipStreamPerThread && !is_capturing(st)) {
+    if (w.done) HIP_TRY(hipStreamWaitEvent(st, w.done, 0));
+    else HIP_TRY(hipEventCreateWithFlags(&w.done, hipEventDisableTiming));
+    folds.done = w.done;
+  }
+  *out = w.buf;
+  return TR_OK;
+}
+
 // Append the sample jobs 1..A-1 of jobs[i] (A = aa[i]) and list the folds.
 static tr_status expand_aa(std::vector<JobDev> &jobs, const std::vector<int32_t> &aa,
-                           hipStream_t st, std::vector<AAMean> &means) {
+                           hipStream_t st, AAFolds &folds) {
   int64_t total = 0;
   for (size_t i = 0; i < aa.size(); ++i)
     if (aa[i] > 1) total += (int64_t)(aa[i] - 1) * jobs[i].W * jobs[i].H * 3;
   if (total == 0) return TR_OK;
   float *ws = nullptr;
-  tr_status rc = aa_workspace(st, total, &ws);
+  tr_status rc = aa_workspace(st, total, folds, &ws);
   if (rc != TR_OK) return rc;
   int64_t off = 0;
   const size_t n0 = aa.size();
@@ -1382,7 +1406,7 @@ static tr_status expand_aa(std::vector<JobDev> &jobs, const std::vector<int32_t>
     if (aa[i] <= 1) continue;
     const JobDev base = jobs[i];
     const int64_t plane = (int64_t)base.W * base.H * 3;
-    means.push_back(AAMean{base.rgb, ws + off, aa[i] - 1, plane});
+    folds.means.push_back(AAMean{base.rgb, ws + off, aa[i] - 1, plane});
     for (int32_t a = 1; a < aa[i]; ++a) {
       JobDev J = base;
       J.aa = a;
@@ -1397,8 +1421,8 @@ static tr_status expand_aa(std::vector<JobDev> &jobs, const std::vector<int32_t>
   return TR_OK;
 }
 
-static tr_status run_aa_means(const std::vector<AAMean> &means, hipStream_t st) {
-  for (const AAMean &m : means)
+static tr_status run_aa_means(const AAFolds &folds, hipStream_t st) {
+  for (const AAMean &m : folds.means)
     HIP_TRY(trh::launch_aa_mean(m.rgb, m.planes, m.n_planes, m.n, st));
   return TR_OK;
 }
@@ -1601,8 +1625,8 @@ extern "C" tr_status tr_render_tuned(const tr_scene *s, const tr_camera *c, cons
   if (rc != TR_OK) return rc;
   hipStream_t st = (hipStream_t)hip_stream;
   std::vector<JobDev> jobs(1, J);
-  std::vector<AAMean> means;
-  rc = expand_aa(jobs, std::vector<int32_t>(1, aa_count(*p)), st, means);
+  AAFolds folds;
+  rc = expand_aa(jobs, std::vector<int32_t>(1, aa_count(*p)), st, folds);
   if (rc != TR_OK) return rc;
   if (p->precision == TR_PREC_FP64) {
     for (const JobDev &Js : jobs) HIP_TRY(trh::launch_render_plain_f64(Js, f->stats, st));
@@ -1610,7 +1634,7 @@ extern "C" tr_status tr_render_tuned(const tr_scene *s, const tr_camera *c, cons
     rc = launch_wave_jobs(jobs, t, f->stats, st);
     if (rc != TR_OK) return rc;
   }
-  return run_aa_means(means, st);
+  return run_aa_means(folds, st);
 }
 
 extern "C" tr_status tr_render(const tr_scene *s, const tr_camera *c, const tr_params *p,
@@ -1679,23 +1703,23 @@ static tr_status batch_impl(int32_t n, const tr_scene *const *scenes, const tr_c
   }
   for (size_t k = 0; k < f64.size(); ++k) {  // plain FP64 jobs: one launch each
     std::vector<JobDev> one(1, f64[k]);
-    std::vector<AAMean> means;
-    rc = expand_aa(one, std::vector<int32_t>(1, aa64[k]), st, means);
+    AAFolds folds;
+    rc = expand_aa(one, std::vector<int32_t>(1, aa64[k]), st, folds);
     if (rc != TR_OK) return rc;
     for (const JobDev &Js : one) HIP_TRY(trh::launch_render_plain_f64(Js, stats64[k], st));
-    rc = run_aa_means(means, st);
+    rc = run_aa_means(folds, st);
     if (rc != TR_OK) return rc;
   }
   if (jobs.empty()) return TR_OK;
-  std::vector<AAMean> means;
-  rc = expand_aa(jobs, aa, st, means);
+  AAFolds folds;
+  rc = expand_aa(jobs, aa, st, folds);
   if (rc != TR_OK) return rc;
   // keep jobs of one scene adjacent so waves rarely switch scenes
   std::stable_sort(jobs.begin(), jobs.end(),
                    [](const JobDev &a, const JobDev &b) { return a.scene_key < b.scene_key; });
   rc = launch_wave_jobs(jobs, t, stats, st);
   if (rc != TR_OK) return rc;
-  return run_aa_means(means, st);
+  return run_aa_means(folds, st);
 }
 
 // ----------------------------------------------- allocation-free batches

@@ -12,14 +12,14 @@ HIP_STREAM_PER_THREAD = 2
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("jobs", [1, 5])
-def test_threads_on_the_per_thread_stream(jobs):
+@pytest.mark.parametrize("jobs,aa", [(1, 1), (5, 1), (1, 4)])
+def test_threads_on_the_per_thread_stream(jobs, aa):
     import torch
     import paper_0801_1500_amd as tr
     scenes = [tr.Scene(scenegen.tiny_scene(seed=4 + k)) for k in range(2)]
     cams = [scenegen.Camera((2.0 * k, 1.0, 30.0), (0.0, 0.0, 0.0), (0.0, 1.0, 0.0), 50.0, 150 + 37 * k, 90)
             for k in range(4)]
-    p = scenegen.Params(ao_samples=8, seed=3)
+    p = scenegen.Params(ao_samples=8, seed=3, aa_samples=aa)
     want = [frame_to_numpy(tr.render(scenes[k % 2], c, p)) for k, c in enumerate(cams)]
     frames = [[[tr.alloc_frame(c) for _ in range(jobs)] for _ in range(12)] for c in cams]
     torch.cuda.synchronize()

@@ -83,6 +83,40 @@ def tables_per_thread_stream(model, tr):
     assert model.model_races() == 0, model.model_races()
 
 
+def planes_per_thread_stream(model, tr):
+    """The workspace of antialiased frames, on the stream that is another one in
+    every thread, at one size and while it grows."""
+    s = tr.Scene(scenegen.tiny_scene(seed=4))
+    for w in (64, 32, 65, 64):
+        for entry, precision in (("render", "fp32_resolve"), ("batch", "fp32_resolve"), ("batch", "fp64")):
+            def work():
+                for _ in range(2):
+                    assert _render(tr, entry, [_job(tr, s, w, 64, precision, aa_samples=3)], 2) == 0
+            t = threading.Thread(target=work)
+            t.start()
+            t.join()
+    assert model.model_races() == 0 and model.model_misuse() == 0
+
+
+def planes_of_two_threads(model, tr):
+    """A frame whose sample jobs are under way keeps the workspace until its
+    folds are enqueued: a larger frame of another thread on the stream waits."""
+    s = tr.Scene(scenegen.tiny_scene(seed=4))
+    def frame(w):
+        assert _render(tr, "render", [_job(tr, s, w, 64, aa_samples=8)], 0x5000) == 0
+    frame(64)
+    model.model_hold_copy()  # (of the first frame's 8 jobs)
+    threads = [threading.Thread(target=frame, args=(w,)) for w in (64, 128)]
+    threads[0].start()
+    model.model_await_held()
+    threads[1].start()
+    threads[1].join(0.5)
+    model.model_release_copy()
+    for t in threads:
+        t.join()
+    assert model.model_misuse() == 0
+
+
 def tables_under_capture(model, tr):
     """Captured renders wait for nothing on the host and leave nothing behind
     that a later render could not wait for."""
@@ -174,7 +208,8 @@ def test_kernel_choice(test):
     hip_model.run("test_host_launch", test)
 
 
-@pytest.mark.parametrize("test", ["tables_per_thread_stream", "tables_under_capture"])
+@pytest.mark.parametrize("test", ["tables_per_thread_stream", "tables_under_capture",
+                                  "planes_per_thread_stream", "planes_of_two_threads"])
 def test_job_tables(test):
     hip_model.run("test_host_launch", test)
 
