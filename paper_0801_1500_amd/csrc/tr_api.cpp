@@ -1846,11 +1846,13 @@ extern "C" int64_t tr_tga_max_bytes(int32_t width, int32_t height) {
 }
 
 // Per-stream scratch of the encoder: row sizes, row offsets, the file size
-// (device) and its pinned read-back.
+// (device) and its pinned read-back.  On hipStreamPerThread, which is another
+// stream in every thread, a call waits on the device for the last file's rows.
 struct TgaWork {
   int64_t *rows = nullptr;  // [2 * cap + 1]: sizes, offsets, total
   int64_t *h_total = nullptr;
   int32_t cap = 0;
+  hipEvent_t written = nullptr;  // hipStreamPerThread: the last file's rows
 };
 static std::map<std::pair<int, hipStream_t>, TgaWork> g_tga_work;
 
@@ -1879,6 +1881,10 @@ extern "C" tr_status tr_frame_encode_tga(const uint8_t *rgb8, int32_t width, int
     w.cap = height;
   }
   if (!w.h_total) HIP_TRY(hipHostMalloc((void **)&w.h_total, sizeof(int64_t), hipHostMallocDefault));
+  if (st == hipStreamPerThread) {
+    if (w.written) HIP_TRY(hipStreamWaitEvent(st, w.written, 0));
+    else HIP_TRY(hipEventCreateWithFlags(&w.written, hipEventDisableTiming));
+  }
   int64_t *row_bytes = w.rows, *row_off = w.rows + w.cap, *total = w.rows + 2 * (int64_t)w.cap;
   HIP_TRY(trh::launch_tga_sizes(rgb8, width, height, row_bytes, row_off, total, w.h_total, st));
   HIP_TRY(hipStreamSynchronize(st));
@@ -1887,6 +1893,7 @@ extern "C" tr_status tr_frame_encode_tga(const uint8_t *rgb8, int32_t width, int
     return fail(TR_EINVAL, "Targa file needs %lld bytes, the buffer holds %lld", (long long)*size,
                 (long long)capacity);
   HIP_TRY(trh::launch_tga_write(rgb8, width, height, row_off, total, out, st));
+  if (st == hipStreamPerThread) HIP_TRY(hipEventRecord(w.written, st));
   return TR_OK;
 }
 

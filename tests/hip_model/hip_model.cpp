@@ -254,6 +254,11 @@ API int hipLaunchKernel(const void *f, Dim3 g, Dim3 b, void **args, size_t, void
   if (n.find("k_cell_scan") != std::string::npos) std::memcpy(*(char **)args[8] + 8, &radius, 8);
   if (n.find("k_put_jobs") != std::string::npos) touch(*(uintptr_t *)args[1], s, id, true);
   if (n.find("k_render_wave") != std::string::npos) touch(*(uintptr_t *)args[0], s, id, false);
+  if (n.find("k_tga_offsets") != std::string::npos) {
+    touch(*(uintptr_t *)args[2], s, id, true);
+    **(int64_t **)args[4] = 0;  // (the file's size)
+  }
+  if (n.find("k_tga_rowsILb1E") != std::string::npos) touch(*(uintptr_t *)args[4], s, id, false);
   if (n.find("k_aa_mean") != std::string::npos) {  // (stands for the renders into the planes too)
     const uintptr_t planes = *(uintptr_t *)args[1];
     auto it = mem.upper_bound(planes);

@@ -98,6 +98,20 @@ def planes_per_thread_stream(model, tr):
     assert model.model_races() == 0 and model.model_misuse() == 0
 
 
+def rows_per_thread_stream(model, tr):
+    """The Targa encoder's row offsets, on the stream that is another one in
+    every thread."""
+    size = C.c_int64()
+    for height in (64, 32, 65, 64):
+        def work():
+            for _ in range(2):
+                assert tr.lib().tr_frame_encode_tga(0x1000000, 64, height, 0x2000000, 1 << 20, C.byref(size), 2) == 0
+        t = threading.Thread(target=work)
+        t.start()
+        t.join()
+    assert model.model_races() == 0
+
+
 def planes_of_two_threads(model, tr):
     """A frame whose sample jobs are under way keeps the workspace until its
     folds are enqueued: a larger frame of another thread on the stream waits."""
@@ -209,7 +223,8 @@ def test_kernel_choice(test):
 
 
 @pytest.mark.parametrize("test", ["tables_per_thread_stream", "tables_under_capture",
-                                  "planes_per_thread_stream", "planes_of_two_threads"])
+                                  "planes_per_thread_stream", "rows_per_thread_stream",
+                                  "planes_of_two_threads"])
 def test_job_tables(test):
     hip_model.run("test_host_launch", test)
 
