@@ -712,6 +712,7 @@ extern "C" tr_status tr_scene_build_bvh(tr_scene *s, void *hip_stream) {
   add_device(s);
   s->bvh_n = 0;
   s->bvh_depth = 0;
+  fill_scene_dev(s);  // (no walk of the old tree if this build fails)
   const int64_t n_nodes = n >= 2 ? n - 1 : 0;
   if (s->bvh_nodes && s->bvh_cap != n_nodes) {
     dev_free(s->bvh_nodes, true);

@@ -120,6 +120,24 @@ def host_out_of_memory(model, tr):
     assert done and model.model_misuse() == 0
 
 
+def failed_bvh(model, tr):
+    """A BVH build that fails leaves no tree to walk, also where there was one."""
+    s = _scene(tr, n=2000)
+    s.build_bvh()
+    def walk():
+        scene, cam, p, f = _job(tr, s, 64, 64)
+        return tr.lib().tr_render_tuned(scene.handle, C.byref(cam), C.byref(p), C.byref(f),
+                                        C.byref(tr.make_tune({"accel": 1})), None)
+    assert walk() == 0
+    model.model_capacity(0, model.model_used(0))
+    with pytest.raises(Exception):
+        _scene(tr, n=300000)  # (the kept blocks are given back)
+    model.model_capacity(0, model.model_used(0))
+    with pytest.raises(Exception):
+        s.build_bvh()
+    assert walk() != 0
+
+
 def changing_sizes(model, tr):
     """Blocks of sizes that do not come back make room for later ones: after
     any mix of scenes the next of a size finds the last one's blocks, and no
@@ -183,7 +201,7 @@ def test_no_exception_leaves():
     hip_model.run("test_host_memory", "host_out_of_memory")
 
 
-@pytest.mark.parametrize("test", ["out_of_memory"])
+@pytest.mark.parametrize("test", ["out_of_memory", "failed_bvh"])
 def test_kept_blocks_are_given_back(test):
     hip_model.run("test_host_memory", test)
 
