@@ -1199,8 +1199,8 @@ static tr_status make_job(const tr_scene *s, const tr_camera *c, const tr_params
   J.light_mask = f->light_mask;
   J.tile_w = tile_w;
   J.tile_h = 64 / tile_w;
-  J.tiles_x = (c->width + tile_w - 1) / tile_w;
-  J.tiles_y = (c->height + J.tile_h - 1) / J.tile_h;
+  J.tiles_x = (int32_t)(((int64_t)c->width + tile_w - 1) / tile_w);
+  J.tiles_y = (int32_t)(((int64_t)c->height + J.tile_h - 1) / J.tile_h);
   J.tile_begin = 0;
   J.tile_end = (int64_t)J.tiles_x * J.tiles_y;
   J.scene_key = s->key;
@@ -1647,7 +1647,7 @@ extern "C" int64_t tr_tile_count(int32_t width, int32_t height, int32_t tile_w) 
   if (tile_w == 0) tile_w = kDefaultTileW;
   if (!valid_tile_w(tile_w) || width <= 0 || height <= 0) return -1;
   const int32_t th = 64 / tile_w;
-  return (int64_t)((width + tile_w - 1) / tile_w) * ((height + th - 1) / th);
+  return (((int64_t)width + tile_w - 1) / tile_w) * (((int64_t)height + th - 1) / th);
 }
 
 static tr_status batch_impl(int32_t n, const tr_scene *const *scenes, const tr_camera *cams,

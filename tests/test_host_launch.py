@@ -52,6 +52,18 @@ def large_fp32(model, tr):
     assert _render(tr, "batch", [_job(tr, s, 1024, 1024)] * 4096) == 0, tr.lib().tr_last_error()
 
 
+def wide(model, tr):
+    """Rows and columns of up to 2^31 - 2 pixels (a tile of the default shape is
+    64 x 1)."""
+    s = tr.Scene(scenegen.tiny_scene(seed=4))
+    for w, h, tiles in ((2 ** 31 - 65, 1, 2 ** 25 - 1), (2 ** 31 - 2, 1, 2 ** 25), (1, 2 ** 31 - 2, 2 ** 31 - 2)):
+        assert tr.tile_count(w, h) == tiles
+        assert _render(tr, "render", [_job(tr, s, w, h)]) == 0, (w, h, tr.lib().tr_last_error())
+        name, grid, _ = hip_model.launches(model)[-1]
+        assert "k_render_wave" in name
+        assert (tiles <= grid < 1.05 * tiles) if tiles < LIMIT else ("ILi2E" in name), (w, h, name, grid)
+
+
 def large_fp64(model, tr):
     """Narrow FP64 frames of 2^26 tiles and more: all entries in launches that
     the runtime takes."""
@@ -229,6 +241,6 @@ def test_job_tables(test):
     hip_model.run("test_host_launch", test)
 
 
-@pytest.mark.parametrize("test", ["large_fp32", "large_fp64"])
+@pytest.mark.parametrize("test", ["large_fp32", "large_fp64", "wide"])
 def test_launch_sizes(test):
     hip_model.run("test_host_launch", test)
